@@ -92,6 +92,14 @@ __device__ inline double wave_sum(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// the sum over each group of 8 consecutive lanes (the first three steps above)
+__device__ inline double group8_sum(double v) {
+    v += dpp_f64<0xb1, 0xf>(v);
+    v += dpp_f64<0x4e, 0xf>(v);
+    v += dpp_f64<0x141, 0xf>(v);
+    return v;
+}
+
 // the same DPP pattern for min and max; lanes of rows outside a row mask
 // receive their own value (min and max have no zero to fall back on)
 template <int CTRL, int ROW_MASK>
@@ -191,6 +199,24 @@ __device__ inline void snap_range(double lo, double hi, double* c_out, double* s
 // itself, so a later pass over the same workspace (the adjoint, the residuals)
 // cuts every fit where the forward pass did, whatever its own launch shape.
 // ---------------------------------------------------------------------------
+// the fit that holds tile t: the largest f with tile_start[f] <= t.  The wave
+// probes 64 entries at a time (tile_start does not decrease and tile_start[0]
+// = 0), so a batch of 65,536 fits takes 3 dependent loads where a search by
+// halves takes 16, each a memory round trip before the wave's first points:
+// 65,536 fits of 16 points went from 13.6 to 11.0 us.
+__device__ inline int64_t find_fit(const int64_t* __restrict__ tile_start, int64_t batch, int64_t t) {
+    int64_t a = 0, n = batch;   // the answer lies in [a, a + n)
+    while (n > 1) {
+        const int64_t step = (n + kWave - 1) / kWave;
+        const int64_t off = (int64_t)lane_id() * step;
+        const bool le = off < n && tile_start[a + off] <= t;
+        const int64_t k = (int64_t)(__popcll(__ballot(le)) - 1) * step;
+        a += k;
+        n = n - k < step ? n - k : step;
+    }
+    return a;
+}
+
 template <class Fn>
 __device__ inline void walk_segments(const FitDesc& d, const int64_t* __restrict__ tile_start, int64_t wave,
                                      int64_t W, Fn&& fn) {
@@ -199,13 +225,7 @@ __device__ inline void walk_segments(const FitDesc& d, const int64_t* __restrict
     const int64_t t0 = wave * NT / W;
     const int64_t t1 = (wave + 1) * NT / W;
     if (t0 >= t1) return;
-    int64_t lo = 0, hi = d.batch;   // largest f with tile_start[f] <= t0
-    while (hi - lo > 1) {
-        int64_t mid = (lo + hi) >> 1;
-        if (tile_start[mid] <= t0) lo = mid;
-        else hi = mid;
-    }
-    int64_t f = lo;
+    int64_t f = find_fit(tile_start, d.batch, t0);
     int64_t t = t0;
     while (t < t1) {
         const int64_t fs = tile_start[f], fe = tile_start[f + 1];
@@ -259,13 +279,7 @@ __device__ inline void walk_segments_ahead(const FitDesc& d, const int64_t* __re
     const int64_t t0 = wave * NT / W;
     const int64_t t1 = (wave + 1) * NT / W;
     if (t0 >= t1) return;
-    int64_t lo = 0, hi = d.batch;   // largest f with tile_start[f] <= t0
-    while (hi - lo > 1) {
-        int64_t mid = (lo + hi) >> 1;
-        if (tile_start[mid] <= t0) lo = mid;
-        else hi = mid;
-    }
-    int64_t f = lo;
+    int64_t f = find_fit(tile_start, d.batch, t0);
     SegMeta cur = load_meta(d, tile_start, pstatus, rec, rl, f);
     int64_t t = t0;
     while (t < t1) {
@@ -284,6 +298,94 @@ __device__ inline void walk_segments_ahead(const FitDesc& d, const int64_t* __re
         fn(f, plo, phi, wave + f, cur);
         t = te;
         ++f;
+        cur = nxt;
+    }
+}
+
+// the same walk with short fits taken several at a time: the wave looks at
+// kGroups consecutive fits together, lanes kGroup g .. kGroup (g+1) - 1 holding
+// the metadata of the g-th.  The short ones among them go to one call of
+// sh(f, mine, meta), made by the whole wave with each lane's own fit (mine:
+// whether it is a short one, lying inside the wave's tiles); the others go to
+// lg(f, lo, hi, slot, meta), one at a time and in order, as walk_segments_ahead
+// passes them.  Fits whose plan status is not OK are skipped.  The next kGroups
+// fits' metadata is loaded before the current ones are streamed.
+//
+// Which fits are short: a fit that a whole wave streams costs about one memory
+// round trip however few its points, and a group of kGroup lanes needs one
+// round trip per kGroupRound bytes of x (and as many of y).  So of c fits that
+// could be taken together, those of at most c round trips are; the most,
+// kGroups round trips, is 1,024 float32 points.  Measured, 65,536 fits of 16 to
+// 256 float32 points (log-uniform, 45 MB): 102 us one fit per wave, 22 us
+// grouped; 16,384 fits of 1,024 points (134 MB): 37.5 and 24 us; 2,048-point
+// fits are faster one at a time (24 us, 31 grouped); 16 lanes per fit are
+// slower below 512 points (32 us on the first batch) and no faster above.
+constexpr int kGroup = 8;                  // lanes of a short fit
+constexpr int kGroups = kWave / kGroup;    // short fits a wave streams at a time
+constexpr int kGroupUnroll = 4;            // 16-byte vectors in flight per lane and array of a short fit
+constexpr int kGroupRound = 16 * kGroup * kGroupUnroll;
+
+__device__ inline int64_t bcast_i64(int64_t v, int src) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, src);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), src);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ inline double bcast(double v, int src) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
+    return __hiloint2double(hi, lo);
+}
+
+// size: bytes of one x
+template <class Short, class Long>
+__device__ inline void walk_grouped(const FitDesc& d, const int64_t* __restrict__ tile_start,
+                                    const int32_t* __restrict__ pstatus, const double* __restrict__ rec, int rl,
+                                    int64_t wave, int64_t W, int size, Short&& sh, Long&& lg) {
+    const int64_t NT = tile_start[d.batch];
+    const int64_t tile = tile_start[d.batch + 1];
+    const int64_t t0 = wave * NT / W;
+    const int64_t t1 = (wave + 1) * NT / W;
+    if (t0 >= t1) return;
+    int64_t f0 = find_fit(tile_start, d.batch, t0);
+    const int g = lane_id() / kGroup;
+    // a lane past the last fit holds the last one again and drops it
+    auto load = [&](int64_t first) {
+        const int64_t f = first + g;
+        return load_meta(d, tile_start, pstatus, rec, rl, f < d.batch ? f : d.batch - 1);
+    };
+    SegMeta cur = load(f0);
+    for (;;) {
+        const bool more = bcast_i64(cur.fe, kWave - 1) < t1;   // then fit f0 + kGroups < B holds the next tile
+        SegMeta nxt = cur;
+        if (more) nxt = load(f0 + kGroups);
+        const bool in = f0 + g < d.batch && cur.st == LSEFIT_OK && cur.fs < t1 && cur.fe > t0 && cur.fs < cur.fe;
+        const int64_t bytes = (cur.hi - cur.lo) * size;
+        const bool could = in && cur.fs >= t0 && cur.fe <= t1 && bytes <= kGroups * kGroupRound;
+        const int c = __popcll(__ballot(could)) / kGroup;
+        const bool mine = could && bytes <= c * kGroupRound;
+        if (__ballot(mine)) sh(f0 + g, mine, cur);
+        uint64_t todo = __ballot(in && !mine) & 0x0101010101010101ull;   // one bit per fit
+        while (todo) {
+            const int src = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            SegMeta m;
+            m.fs = bcast_i64(cur.fs, src);
+            m.fe = bcast_i64(cur.fe, src);
+            m.lo = bcast_i64(cur.lo, src);
+            m.hi = bcast_i64(cur.hi, src);
+            m.c = bcast(cur.c, src);
+            m.s = bcast(cur.s, src);
+            m.st = LSEFIT_OK;
+            m.deg = __builtin_amdgcn_readlane(cur.deg, src);
+            const int64_t f = f0 + src / kGroup;
+            const int64_t tb = m.fs > t0 ? m.fs : t0, te = m.fe < t1 ? m.fe : t1;
+            const int64_t plo = m.lo + (tb - m.fs) * tile;
+            int64_t phi = m.lo + (te - m.fs) * tile;
+            if (phi > m.hi) phi = m.hi;
+            lg(f, plo, phi, wave + f, m);
+        }
+        if (!more) break;
+        f0 += kGroups;
         cur = nxt;
     }
 }
@@ -491,12 +593,6 @@ __device__ inline void to_x_basis(const double (&b)[N], double c, double s, doub
 // The same operations, in the same order per entry, as the one-thread
 // solvers above.
 // ---------------------------------------------------------------------------
-__device__ inline double bcast(double v, int src) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-    return __hiloint2double(hi, lo);
-}
-
 // v[k] = sh[0][k] + sh[1][k] + ... + sh[nw-1][k] (in that order) in every
 // lane of the calling wave: lane k adds column k, readlane shares the sums
 // (K <= 64)

@@ -247,6 +247,47 @@ __device__ inline void stream_segment(const In* __restrict__ x, const In* __rest
     }
 }
 
+// kGroup lanes stream one short fit's points [lo, lo + n) into an accumulator
+// (a lane whose fit is not short has n = 0).  The loads are
+// 16 bytes at the alignment of one element, which the vector memory path
+// takes as it is, so a fit that starts anywhere needs no head; its last
+// n mod VW points are loaded with the first round.  Every lane issues the
+// same loads -- a lane past its fit's vectors reads the last one again and
+// drops it -- so that a round is one memory round trip for all kGroups fits.
+template <typename In>
+struct VecAny {
+    typedef typename VecOf<In>::type type __attribute__((aligned(sizeof(In))));
+};
+
+template <int U, typename In, class Acc>
+__device__ inline void stream_group(const In* __restrict__ x, const In* __restrict__ y, int64_t lo, int n, Acc& acc) {
+    constexpr int VW = VecOf<In>::W;
+    using V = typename VecOf<In>::type;
+    using VA = typename VecAny<In>::type;
+    const int gl = lane_id() % kGroup;
+    const int nv = n / VW, tail = n - nv * VW;
+    const In* px = x + lo;
+    const In* py = y + lo;
+    In tx = 0, ty = 0;
+    if (gl < tail) {
+        tx = ld_scalar(px + nv * VW + gl);
+        ty = ld_scalar(py + nv * VW + gl);
+    }
+    for (int j = gl; j < nv; j += kGroup * U) {
+        V xs[U], ys[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(j + u * kGroup, nv - 1) * VW;
+            xs[u] = *reinterpret_cast<const VA*>(px + i);
+            ys[u] = *reinterpret_cast<const VA*>(py + i);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u * kGroup < nv) acc.template vec<V, VW>(xs[u], ys[u]);
+    }
+    if (gl < tail) acc.scalar(tx, ty);
+}
+
 // single fit: the whole grid strides over the 16-byte vectors of x and y (wave
 // g reads vectors g*64 + lane, then every W*64 further), so consecutive waves
 // read consecutive kilobytes and the grid sweeps the arrays front to back.
@@ -816,9 +857,29 @@ __global__ void __launch_bounds__(256)
         dispatch_degree<MAXM>(d.degree, body);
         return;
     }
-    walk_segments_ahead(d, w.tile_start, w.pstatus, w.rec, rl, wave, W,
-                        [&](int64_t f, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
-        if (mt.st != LSEFIT_OK) return;
+    // short fits, kGroups at a time: every lane accumulates the sums of the
+    // largest degree (a fit of degree m has the first 2m and m + 1 of them)
+    auto short_fits = [&](int64_t f, bool mine, const SegMeta& mt) {
+        using Acc = std::conditional_t<PREC == LSEFIT_PREC_F64, AccF64<MAXM>, AccF32C<MAXM>>;
+        Acc acc;
+        acc.init(mt.c, 1.0 / mt.s);
+        stream_group<kGroupUnroll>(x, y, mt.lo, mine ? (int)(mt.hi - mt.lo) : 0, acc);
+        double v[stride];
+        acc.out(v);
+#pragma unroll
+        for (int k = 0; k < stride; ++k) v[k] = group8_sum(v[k]);
+        double* __restrict__ out = w.part + (wave + f) * stride;
+        if (mine && lane_id() % kGroup == 0) {
+#pragma unroll
+            for (int k = 0; k < 2 * MAXM; ++k)
+                if (k < 2 * mt.deg) out[k] = v[k];
+#pragma unroll
+            for (int j = 0; j <= MAXM; ++j)
+                if (j <= mt.deg) out[2 * mt.deg + j] = v[2 * MAXM + j];
+        }
+    };
+    walk_grouped(d, w.tile_start, w.pstatus, w.rec, rl, wave, W, (int)sizeof(In), short_fits,
+                 [&](int64_t f, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
         const double inv_s = 1.0 / mt.s;
         double* __restrict__ out = w.part + slot * stride;
         auto body = [&]<int M>() {
@@ -1208,13 +1269,7 @@ __global__ void __launch_bounds__(256)
     const int64_t first = (int64_t)wave_id_in_block() * kWave + lane_id();
     const int64_t step = (int64_t)(blockDim.x / kWave) * kWave;
     const bool edge = wave_id_in_block() == 0;
-    int64_t lo = 0, hi = d.batch;   // largest f with tile_start[f] <= t0
-    while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (w.tile_start[mid] <= t0) lo = mid;
-        else hi = mid;
-    }
-    int64_t f = lo;
+    int64_t f = find_fit(w.tile_start, d.batch, t0);
     AdjMeta<MAXM, SOLVE> cur = load_adj_meta<MAXM, SOLVE>(d, w, f, gcoef, coef_stride);
     int64_t t = t0;
     while (t < t1) {

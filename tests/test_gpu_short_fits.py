@@ -1,0 +1,86 @@
+"""Batches of short fits: a wave takes up to 8 neighbouring fits together, 8 lanes
+each, when they are short enough for their number (at most 512 bytes of x per fit
+taken together; float32: 128 points alone, 1,024 when 8 are).  The sizes below sit
+at the edges of that rule, of the 16-byte vectors and of the rounds of 4 vectors per
+lane, in batches whose last group of fits is full, one short of full and one over."""
+import numpy as np
+import pytest
+
+from gpu_common import announce, normwise, to_dev, torch
+from oracle import fp64
+from paper_1512_08017_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+lf = pytest.importorskip("paper_1512_08017_amd")
+EPS = np.finfo(np.float64).eps
+
+EDGES = [3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 130, 131, 255, 256, 257, 383, 511, 512, 513,
+         640, 1023, 1024, 1025, 1500, 2047, 2048, 2049, 5000]
+
+
+def lengths(count, seed):
+    """Runs of one size (whole groups of it) and sizes at random, empty fits among them."""
+    rng = np.random.default_rng(seed)
+    runs = np.concatenate([np.full(k, n) for n in (16, 128, 129, 256, 512, 513, 1024, 1025) for k in (1, 2, 9)])
+    some = rng.choice(EDGES + [0, 1, 2], 120)
+    return np.concatenate([runs, some, rng.choice([20, 100, 1000], count)])
+
+
+def gate(x, m, c, s):
+    """Both sides solve the same normal system, each with its own rounding of the sums."""
+    V = np.vander((x.astype(np.float64) - c) / s, m + 1, increasing=True)
+    return max(1e-12, 1e3 * EPS * np.linalg.cond(V.T @ V))
+
+
+@pytest.mark.parametrize("dtype,maxdeg,count,shift", [(np.float32, 3, 8, 0), (np.float32, 5, 7, 1), (np.float64, 2, 1, 0),
+                                                      (np.float64, 4, 9, 1), (np.float32, 1, 15, 2)])
+def test_short_fits_against_oracle(dtype, maxdeg, count, shift):
+    """shift 1: x starts one element in (every fit misaligned alike); 2: x and y differently."""
+    announce(f"short fits {np.dtype(dtype).name} degree <= {maxdeg} count {count} shift {shift}")
+    n = lengths(count, 40 + maxdeg)
+    deg = np.random.default_rng(count).integers(1, maxdeg + 1, n.size).astype(np.int32)
+    bf = W.random_batch(n, deg, seed=50 + maxdeg, dtype=dtype)
+    pad = np.zeros(2, dtype)
+    x = to_dev(np.concatenate([pad[:shift], bf.x]))[shift:]
+    y = to_dev(np.concatenate([pad[:1 if shift else 0], bf.y]))[1 if shift else 0:]
+    coef, status, _ = lf.fit_batched(x, y, to_dev(bf.offsets), to_dev(bf.degrees), maxdeg, center=0.0, scale=1.0)
+    torch.cuda.synchronize()
+    coef, status = coef.cpu().numpy(), status.cpu().numpy()
+    for f in range(bf.batch):
+        m, lo, hi = int(deg[f]), bf.offsets[f], bf.offsets[f + 1]
+        if hi - lo < m + 1:
+            assert status[f] == 2 and np.isnan(coef[f, : m + 1]).all(), (f, hi - lo, status[f])
+            continue
+        tol = gate(bf.x[lo:hi], m, 0.0, 1.0)
+        if tol > 1e-3:        # a handful of points nearly on top of each other
+            continue
+        ref = fp64.fit(bf.x[lo:hi], bf.y[lo:hi], m)
+        assert status[f] == 0, (f, hi - lo, m, status[f])
+        e = normwise(coef[f, : m + 1], np.asarray(ref["a"], float))
+        assert e <= tol, (f, hi - lo, m, e, tol)
+        assert (coef[f, m + 1:] == 0).all()
+
+
+def test_short_fits_compensated():
+    """float32 sums of degree <= 2 with the refinement pass: an error of 2^-23 cond(A) before the
+    refinement leaves about its square after it, below 1e-6 for cond(A) <= 1e3."""
+    announce("short fits, compensated float32")
+    n = lengths(9, 60)
+    deg = np.random.default_rng(61).integers(1, 3, n.size).astype(np.int32)
+    bf = W.random_batch(n, deg, seed=62)
+    coef, status, _ = lf.fit_batched(to_dev(bf.x), to_dev(bf.y), to_dev(bf.offsets), to_dev(bf.degrees), 2,
+                                     precision="f32c", center=0.0, scale=1.0)
+    torch.cuda.synchronize()
+    coef, status = coef.cpu().numpy(), status.cpu().numpy()
+    done = 0
+    for f in range(bf.batch):
+        m, lo, hi = int(deg[f]), bf.offsets[f], bf.offsets[f + 1]
+        if hi - lo < m + 1 or gate(bf.x[lo:hi], m, 0.0, 1.0) > 1e3 * EPS * 1e3:
+            continue
+        ref = fp64.fit(bf.x[lo:hi], bf.y[lo:hi], m)
+        assert status[f] == 0
+        e = normwise(coef[f, : m + 1], np.asarray(ref["a"], float))
+        assert e <= 1e-6, (f, hi - lo, m, e)
+        done += 1
+    assert done > 100
