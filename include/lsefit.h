@@ -257,13 +257,20 @@ lsefit_status fit_single_noalloc(const void* x, const void* y, int64_t n, int32_
 
 /* One fit through an orthogonal factorisation instead of the normal equations
  * (the QR route of Sec. III, which Sec. V's "methods other than Gaussian
- * elimination" points to): every lane of the streaming pass keeps a triangular
- * factor of the rows (1, t, .., t^m | y) it reads, updated with square-root-free
- * Givens rotations (Gentleman), and the factors are merged lane -> wave ->
- * block -> fit in a fixed order (a tall-skinny tree).  The error is governed by
- * cond(V), V_ik = t_i^k, not by cond(V)^2 as for the power sums; the pass costs
- * about (m+1)(m+2)/2 + 12(m+1) float64 operations per point instead of the
- * 5m+1 of the power sums.
+ * elimination" points to).  The error is governed by cond(V), V_ik = t_i^k, not
+ * by cond(V)^2 as for the power sums.  Two routes to the same factor:
+ *  - every lane of the streaming pass keeps a triangular factor of the rows
+ *    (1, t, .., t^m | y) it reads, updated with square-root-free Givens rotations
+ *    (Gentleman), and the factors are merged lane -> wave -> block -> fit in a
+ *    fixed order (a tall-skinny tree): about (m+1)(m+2)/2 + 12(m+1) float64
+ *    operations per point;
+ *  - from 1,024 points on (2^21 at degree 2, 2^23 at degree 1) the pass first
+ *    sums the Gram matrix of the polynomials that are orthogonal over the 256
+ *    range samples, near the identity wherever the sample stands for the points,
+ *    and the right sides of what the sample's own fit leaves (7m+1 float64
+ *    operations per point); its Cholesky factor times the sample's triangle is
+ *    R.  When the sample does not stand for the points (the pivots tell), a third
+ *    launch, empty otherwise, runs the rotations.
  *  x, y, n, dt, ws: as fit_single (same workspace size)
  *  opt:      degree 1..LSEFIT_MAX_DEGREE, range (as fit_single); precision
  *            must be LSEFIT_PREC_F64 and basis monomial (else UNSUPPORTED);
@@ -440,7 +447,8 @@ lsefit_status lsefit_copy_probe(const float* x, const float* y, float* ox, float
  * clears the totals and the pool; lsefit_timing_read waits for the device and
  * returns the summed duration of one kernel kind in milliseconds and the
  * number of timed launches since the last reset.
- *  kind: 0 = power-sum pass (k_moments, or the Chebyshev / QR streaming pass),
+ *  kind: 0 = power-sum pass (k_moments, or the Chebyshev / QR streaming pass; of
+ *        fit_qr's two routes the first one tried),
  *        1 = refinement pass, 2 = adjoint streaming pass (not its per-fit
  *        solve), 3 = per-fit combine and solve (the finish kernel of a single
  *        fit), 4 = read or copy probe, 5 = residual pass (not its per-fit

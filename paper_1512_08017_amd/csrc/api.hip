@@ -625,6 +625,19 @@ lsefit_status fit_single_noalloc(const void* x, const void* y, int64_t n, int32_
     return enqueue_single(x, y, n, dt, opt, ws, lay, sched, coef, status, moments, (hipStream_t)stream);
 }
 
+// Whether a single QR fit takes the sampled route first.  It has three launches
+// where the rotations alone have two, so on small fits of degree 1 and 2, where
+// the host's launches are all that counts, the rotations stay ahead (1e6
+// float32 points, m = 1: 18 us against 22; m = 2: 20 against 22; at 4e6 points
+// m = 2 turns to 26 against 22, m = 1 at about 6e6).  From degree 3 on the
+// rotations' merge tree alone costs more than the third launch at every size (20,000
+// points, m = 3: 28 us against 22; m = 8: 290 against 24; 1e7 points, m = 5: 92
+// against 33); the route needs more points than its sample of 256.
+bool qr_sampled(int64_t n, int degree) {
+    const int64_t from = degree == 1 ? (int64_t)1 << 23 : (degree == 2 ? (int64_t)1 << 21 : 1024);
+    return n >= from;
+}
+
 lsefit_status fit_qr(const void* x, const void* y, int64_t n, int32_t dt, const lsefit_options* opt, void* ws,
                      size_t ws_bytes, double* coef, int32_t* status, double* info, void* stream) {
     if (!coef || !status) return LSEFIT_ERR_INVALID_ARG;
@@ -639,6 +652,14 @@ lsefit_status fit_qr(const void* x, const void* y, int64_t n, int32_t dt, const 
     const Launch L = to_launch(sched);
     const int mis = common_mis(dt, {x, y});
     const RangeArg ra{opt->range_mode, opt->center, opt->scale};
+    if (qr_sampled(n, opt->degree)) {
+        LSEFIT_TRY(timed(kTimeMoments, st, [&] { return launch_qr_sampled(d, w, dt, x, y, L, mis, ra, st); }));
+        LSEFIT_TRY(timed(kTimeCombine, st, [&] {
+            return launch_qr_sampled_finish(d, w, grid_blocks(L), coef, status, info, st);
+        }));
+        LSEFIT_TRY(launch_qr_if_left(d, w, dt, x, y, L, mis, ra, coef, status, info, st));
+        return LSEFIT_OK;
+    }
     LSEFIT_TRY(timed(kTimeMoments, st, [&] { return launch_qr_single(d, w, dt, x, y, L, mis, ra, st); }));
     LSEFIT_TRY(timed(kTimeCombine, st,
                      [&] { return launch_qr_finish(d, w, grid_blocks(L), coef, status, info, st); }));

@@ -157,6 +157,17 @@ hipError_t launch_qr_single(const FitDesc& d, const Work& w, int dtype, const vo
                             const Launch& L, int mis, const RangeArg& ra, hipStream_t st);
 hipError_t launch_qr_finish(const FitDesc& d, const Work& w, int64_t G, double* coef, int32_t* status, double* info,
                             hipStream_t st);
+// The sampled route of a larger fit (n_single > 256): per-block sums of the
+// Gram matrix in the sample's orthogonal polynomials into w.part, then one
+// block solves and writes the same, or leaves the fit to the third launch, the
+// rotations in one kernel, which otherwise returns at once.
+hipError_t launch_qr_sampled(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y,
+                             const Launch& L, int mis, const RangeArg& ra, hipStream_t st);
+hipError_t launch_qr_sampled_finish(const FitDesc& d, const Work& w, int64_t G, double* coef, int32_t* status,
+                                    double* info, hipStream_t st);
+hipError_t launch_qr_if_left(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y,
+                             const Launch& L, int mis, const RangeArg& ra, double* coef, int32_t* status,
+                             double* info, hipStream_t st);
 // Streaming QR of a batch: per-(wave, fit) factors into w.part (after the tile
 // table), then one thread per fit merges, solves and writes a, status, sse.
 hipError_t launch_qr_batch(const FitDesc& d, const Work& w, int maxm, int dtype, const void* x, const void* y,

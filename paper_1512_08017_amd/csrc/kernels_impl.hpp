@@ -760,6 +760,16 @@ __global__ void __launch_bounds__(kFinishWaves * kWave) k_finish_single(FitDesc 
 // ---------------------------------------------------------------------------
 constexpr int kSingleRangeSamples = 256;
 
+// position of range sample i of n > kSingleRangeSamples points,
+// floor(i (n - 1) / (kSingleRangeSamples - 1)), with n - 1 split once per wave so
+// that no lane divides 64-bit integers (a call's first microsecond otherwise)
+__device__ inline int64_t sample_at(int i, int64_t n) {
+    constexpr int D = kSingleRangeSamples - 1;
+    const int64_t q = (n - 1) / D;
+    const int r = (int)((n - 1) - q * D);
+    return i * q + (unsigned)(i * r) / (unsigned)D;
+}
+
 template <typename In>
 __device__ inline void single_range(const FitDesc& d, const Work& w, const In* __restrict__ x, const RangeArg& ra,
                                     double* c_out, double* inv_s_out) {
@@ -767,14 +777,14 @@ __device__ inline void single_range(const FitDesc& d, const Work& w, const In* _
     double c = ra.c, s = ra.s;
     if (ra.mode == LSEFIT_RANGE_AUTO) {
         const int64_t n = d.n_single;
-        const int64_t K = n < kSingleRangeSamples ? n : kSingleRangeSamples;
+        const int K = n < kSingleRangeSamples ? (int)n : kSingleRangeSamples;
         double lo = INFINITY, hi = -INFINITY;
         double v[kSingleRangeSamples / kWave];
 #pragma unroll
         for (int j = 0; j < kSingleRangeSamples / kWave; ++j) {
-            const int64_t i = threadIdx.x + (int64_t)j * blockDim.x;
+            const int i = threadIdx.x + j * blockDim.x;
             v[j] = NAN;
-            if (i < K) v[j] = (double)x[K == 1 ? 0 : i * (n - 1) / (K - 1)];
+            if (i < K) v[j] = (double)x[n <= kSingleRangeSamples ? (int64_t)i : sample_at(i, n)];
         }
 #pragma unroll
         for (int j = 0; j < kSingleRangeSamples / kWave; ++j) {

@@ -15,6 +15,19 @@
 // is Rb_ik + sb x_k' with the already reduced x_k' (one multiply-add).  Two
 // factors merge by including the rows of one, (weight d_i, row Rb_i, right
 // side th_i), into the other.
+//
+// A single fit large enough for it (qr_sampled in api.hip) first tries a shorter route to the
+// same R and solution, a Cholesky factorisation of a Gram matrix that is near
+// the identity to begin with (k_qr_sampled, k_qr_sampled_finish): every wave
+// orthogonalises the powers of t over the range sample of the points (the
+// discrete orthogonal polynomials p_0..p_m of the sample, by Stieltjes'
+// three-term recurrence), fits the sample in them, and the pass sums the Gram
+// matrix of p_0..p_m and the right sides of the remaining residual over all the
+// points.  With P = [p_k(t_i)] the factor of V is R = chol(P^T P) R_sample, and
+// cond(P) is near 1 wherever the sample stands for the points, so squaring it
+// costs nothing and the error is governed by cond(V) as in the rotations.  The
+// finish checks exactly that (the pivots of P^T P against the sample's norms) and
+// else leaves the fit to the rotations, which need no assumption.
 #include "kernels_impl.hpp"
 
 namespace lsefit {
@@ -260,10 +273,8 @@ __device__ inline void block_merge_store(const Work& w, GivensQR<N>& q) {
 constexpr int qr_waves_per_eu(int M) { return M <= 3 ? 5 : (M <= 4 ? 4 : 2); }
 
 template <typename In, int U, int M>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_waves_per_eu(M))))
-    k_qr_single(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
-                RangeArg ra) {
-    const KernelClock kclock_(w.clock);
+__device__ __forceinline__ void qr_single_pass(const FitDesc& d, const Work& w, const In* __restrict__ x,
+                                      const In* __restrict__ y, int64_t W, int mis, const RangeArg& ra) {
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
     double c, inv_s;
     single_range(d, w, x, ra, &c, &inv_s);
@@ -273,6 +284,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_wav
     acc.init(c, inv_s, tab);
     stream_strided<U>(x, y, d.n_single, mis, wave, W, acc);
     block_merge_store<M + 1>(w, acc.q);
+}
+
+template <typename In, int U, int M>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_waves_per_eu(M))))
+    k_qr_single(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
+                RangeArg ra) {
+    const KernelClock kclock_(w.clock);
+    qr_single_pass<In, U, M>(d, w, x, y, W, mis, ra);
 }
 
 // Solve Rb b = th for a merged factor of npts rows and write a_0..a_m to out
@@ -324,14 +343,12 @@ __device__ inline int qr_solve_store(const GivensQR<N>& q, int64_t npts, double 
     return st;
 }
 
-// Merge the G block factors (thread t takes blocks t, t + 256, ..., in order;
-// then lanes, then waves, in order), solve, and write [a | b], the status and,
-// if asked, info = [c, s, e].
+// Merge the G block factors (thread t takes blocks t, t + T, ... of the block's
+// T <= 256 threads, in order; then lanes, then waves, in order), solve, and
+// write [a | b], the status and, if asked, info = [c, s, e].
 template <int M>
-__global__ void __launch_bounds__(256)
-    k_qr_finish(FitDesc d, Work w, int64_t G, int maxm, double* __restrict__ coef, int32_t* __restrict__ status,
-                double* __restrict__ info) {
-    const KernelClock kclock_(w.clock);
+__device__ inline void qr_finish_block(const FitDesc& d, const Work& w, int64_t G, int maxm, double* __restrict__ coef,
+                                       int32_t* __restrict__ status, double* __restrict__ info) {
     constexpr int N = M + 1;
     constexpr int LEN = GivensQR<N>::LEN;
     __shared__ double sh[4][LEN];
@@ -356,6 +373,380 @@ __global__ void __launch_bounds__(256)
         info[0] = r[0];
         info[1] = r[1];
         info[2] = st == LSEFIT_OK ? q.e : NAN;
+    }
+}
+
+template <int M>
+__global__ void __launch_bounds__(256)
+    k_qr_finish(FitDesc d, Work w, int64_t G, int maxm, double* __restrict__ coef, int32_t* __restrict__ status,
+                double* __restrict__ info) {
+    const KernelClock kclock_(w.clock);
+    qr_finish_block<M>(d, w, G, maxm, coef, status, info);
+}
+
+// The rotations for a fit that the sampled route has left to them (the first
+// word of w.tile_start, unused by a single fit otherwise, is not zero; else the
+// kernel returns at once).  One launch, so that an accepted fit pays for one empty
+// launch and not two: the last block to store its factor (counted in the
+// second word, which the sampled route's finish has cleared) merges and solves.
+// No block waits for another.  The fences make every block's factor visible to
+// the last one; they cost tens of microseconds here, on the route that is
+// seldom taken.
+template <typename In, int U, int M>
+__global__ void __launch_bounds__(256)
+    k_qr_if_left(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
+                 RangeArg ra, double* __restrict__ coef, int32_t* __restrict__ status, double* __restrict__ info) {
+    if (w.tile_start[0] == 0) return;
+    qr_single_pass<In, U, M>(d, w, x, y, W, mis, ra);
+    __shared__ bool last;
+    __syncthreads();   // thread 0 has stored the block's factor
+    if (threadIdx.x == 0) {
+        __threadfence();
+        const unsigned long long before = atomicAdd((unsigned long long*)&w.tile_start[1], 1ull);
+        last = before + 1 == gridDim.x;
+        __threadfence();
+    }
+    __syncthreads();
+    if (!last) return;
+    qr_finish_block<M>(d, w, gridDim.x, M, coef, status, info);
+}
+
+// ---------------------------------------------------------------------------
+// the sampled route of a single fit
+// ---------------------------------------------------------------------------
+
+// Sums of the pass: with p_0..p_m the sample's polynomials, sum p_k (m), sum
+// p_k p_m (m), sum r p_k (m + 1) and sum r^2.  The rest of the Gram matrix follows from
+// the recurrence, as in the Chebyshev basis: since (t - al_k) p_k = ga_k (p_(k+1) +
+// p_(k-1)), taking <p_j, t p_k> both ways gives
+//   G_(j+1),k = (ga_k (G_j,(k+1) + G_j,(k-1)) + (al_k - al_j) G_jk) / ga_j - G_(j-1),k,
+// which fills row j + 1 from the two above it, its last entry summed.  That is 7m - 1
+// float64 operations per point (with the two conversions 36 at m = 5, 57 at m = 8)
+// where all m (m + 1) / 2 products take 6m + 1 + m (m + 1) / 2 of them, and
+// the rotations about (m + 1)(m + 2) + 12 m.
+__host__ __device__ constexpr int gram_len(int m) { return 3 * m + 2; }
+
+// The sample's polynomials, orthogonal over it and scaled so that their
+// recurrence is p_(k+1) = ((t - al_k) / ga_k) p_k - p_(k-1) (two multiply-adds
+// per point, as (t - al_k) / ga_k is affine in x), p_1 = t - al_0, and the fit of the
+// sample in them, sum_k de_k p_k.  Orthogonality to p_(k-1) sets
+// ga_k = ga_(k-1) |p_k|^2 / |p_(k-1)|^2.  Every wave computes them from the same
+// samples (those of single_range, which its rule for (c, s) also takes), so they
+// are the same bits everywhere.  A sample with too few distinct t, or a
+// non-finite one, gives NaN, which the finish sees in the sums.
+template <int M>
+struct SampleBasis {
+    double al[M], ga[M], de[M + 1];
+    double last;   // |p_M|^2 / |p_(M-1)|^2
+    double c, s;
+
+    // the samples are loaded once, x and y together, for the range and the basis
+    template <typename In>
+    __device__ inline void build(const In* __restrict__ x, const In* __restrict__ y, int64_t n, const RangeArg& ra) {
+        constexpr int J = kSingleRangeSamples / kWave;
+        double t[J], r[J], p[J], pp[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int64_t i = sample_at(lane_id() + j * kWave, n);
+            t[j] = (double)x[i];
+            r[j] = (double)y[i];
+        }
+        c = ra.c;
+        s = ra.s;
+        if (ra.mode == LSEFIT_RANGE_AUTO) {
+            double lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                if (isfinite(t[j])) {
+                    lo = fmin(lo, t[j]);
+                    hi = fmax(hi, t[j]);
+                }
+            }
+            snap_range(wave_min(lo), wave_max(hi), &c, &s);
+        }
+        const double inv_s = 1.0 / s, nc = -c * inv_s;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            t[j] = fma(t[j], inv_s, nc);
+            p[j] = 1.0;
+            pp[j] = 0.0;
+        }
+        double before = 1.0;   // 1 / |p_(k-1)|^2
+#pragma unroll
+        for (int k = 0; k <= M; ++k) {
+            double nu = 0.0, tp = 0.0, rp = 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const double sq = p[j] * p[j];
+                nu += sq;
+                tp = fma(t[j], sq, tp);
+                rp = fma(r[j], p[j], rp);
+            }
+            nu = wave_sum(nu);
+            rp = wave_sum(rp);
+            const double inv = recip(nu);
+            const double ratio = nu * before;
+            before = inv;
+            de[k] = rp * inv;
+            if (k < M) {
+                al[k] = wave_sum(tp) * inv;
+                ga[k] = k > 0 ? ga[k > 0 ? k - 1 : 0] * ratio : 1.0;
+                const double step = recip(ga[k]);
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    r[j] = fma(-de[k], p[j], r[j]);
+                    const double pn = fma((t[j] - al[k]) * step, p[j], -pp[j]);
+                    pp[j] = p[j];
+                    p[j] = pn;
+                }
+            } else {
+                last = ratio;
+            }
+        }
+    }
+};
+
+template <int M>
+struct AccGram {
+    double S[M], H[M], R[M + 1], E;
+    double u1[M], u0[M], nd[M + 1];   // (t - al_k) / ga_k = u1 x + u0; -de_k
+    __device__ inline void init(const SampleBasis<M>& b) {
+#pragma unroll
+        for (int k = 0; k < M; ++k) S[k] = H[k] = 0.0;
+#pragma unroll
+        for (int k = 0; k <= M; ++k) R[k] = 0.0;
+        E = 0.0;
+        const double inv_s = 1.0 / b.s, nc = -b.c * inv_s;
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            const double step = recip(b.ga[k]);
+            u1[k] = inv_s * step;
+            u0[k] = (nc - b.al[k]) * step;
+        }
+#pragma unroll
+        for (int k = 0; k <= M; ++k) nd[k] = -b.de[k];
+    }
+    __device__ inline void point(double xv, double yv) {
+        double p[M + 1];
+        p[0] = 1.0;
+        p[1] = fma(xv, u1[0], u0[0]);
+#pragma unroll
+        for (int k = 1; k < M; ++k) p[k + 1] = fma(fma(xv, u1[k], u0[k]), p[k], -p[k - 1]);
+        double r = yv + nd[0];
+#pragma unroll
+        for (int k = 1; k <= M; ++k) r = fma(nd[k], p[k], r);
+        R[0] += r;
+        E = fma(r, r, E);
+#pragma unroll
+        for (int k = 1; k <= M; ++k) {
+            S[k - 1] += p[k];
+            H[k - 1] = fma(p[k], p[M], H[k - 1]);
+            R[k] = fma(r, p[k], R[k]);
+        }
+    }
+    template <typename V, int VW>
+    __device__ inline void vec(const V& xv, const V& yv) {
+#pragma unroll
+        for (int e = 0; e < VW; ++e) point((double)xv[e], (double)yv[e]);
+    }
+    __device__ inline void scalar(double xv, double yv) { point(xv, yv); }
+    __device__ inline void out(double (&v)[gram_len(M)]) const {
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            v[k] = S[k];
+            v[M + k] = H[k];
+        }
+#pragma unroll
+        for (int k = 0; k <= M; ++k) v[2 * M + k] = R[k];
+        v[3 * M + 1] = E;
+    }
+};
+
+// The pass: the sweep of the power sums, its prologue the sample basis in every
+// wave (about 0.7 us a degree, a chain of wave sums, behind the first loads).
+// Measured against the rotations: 1e8 float32 points, m = 3, 299 -> 121 us (6.6 TB/s,
+// near the sweep's own bound); 1e7 points, m = 5, 69 -> 22 us and m = 8, 870 -> 31 us
+// (float64 issue); the finish 20 -> 4.2 us at m = 5 and 107 -> 6.2 us at m = 8.
+template <typename In, int U, int M>
+__global__ void __launch_bounds__(256)
+    k_qr_sampled(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
+                 RangeArg ra) {
+    const KernelClock kclock_(w.clock);
+    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
+    AccGram<M> acc;
+    SampleBasis<M> b;
+    // range and sample basis while the first loads are in flight
+    stream_strided<U, true>(x, y, d.n_single, mis, wave, W, acc, [&] {
+        b.build(x, y, d.n_single, ra);
+        acc.init(b);
+    });
+    if (wave == 0 && lane_id() == 0) {
+        double* r = w.rec;
+        r[0] = b.c;
+        r[1] = b.s;
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            r[rec_S(M) + k] = b.al[k];
+            r[rec_S(M) + M + k] = b.ga[k];
+        }
+        r[rec_S(M) + 2 * M] = b.last;
+#pragma unroll
+        for (int k = 0; k <= M; ++k) r[rec_lam(M) + k] = b.de[k];
+    }
+    double v[gram_len(M)];
+    acc.out(v);
+#pragma unroll
+    for (int k = 0; k < gram_len(M); ++k) v[k] = wave_sum(v[k]);
+    single_block_partial<gram_len(M), gram_len(M)>(w, v);
+}
+
+// Sum the block partials, fill the Gram matrix and solve: L D L^T = P^T P, the
+// correction of the sample's fit, the residual sum of squares
+// sum r^2 - |D^(-1/2) L^-1 P^T r|^2, and the change from p to powers of t and x.
+// Accepted when
+//  - every number is finite;
+//  - every pivot D_k lies within 2^-6 .. 2^6 of what the sample says,
+//    n / K |p_k|^2: then cond(P^T P), scaled, is a few thousand at most, and
+//    the correction, a fraction of the sample's error, loses no digit that the
+//    rotations would keep;
+//  - the be_k = ga_k ga_(k-1) of the monic recurrence (1/4 of the squared half-range
+//    for smooth densities, k s^2 for a normal one) lie within 2^8 of each other,
+//    so that filling the matrix scales no entry's rounding by more than 2^4 a row;
+//  - the correction takes less than 63/64 of sum r^2: then the difference is
+//    good to 64 roundings;
+//  - |R_kk|, R_kk^2 = D_k times the squared leading coefficient, stays above 2^-36
+//    of the largest: 16 times clear of the singular rule.
+// Otherwise w.tile_start[0] tells the rotations to run.
+template <int M>
+__global__ void __launch_bounds__(kFinishWaves * kWave)
+    k_qr_sampled_finish(FitDesc d, Work w, int64_t G, double* __restrict__ coef, int32_t* __restrict__ status,
+                        double* __restrict__ info) {
+    const KernelClock kclock_(w.clock);
+    constexpr int N = M + 1;
+    constexpr int K = gram_len(M);
+    constexpr int rl = rec_len(M);
+    __shared__ double sums[K];
+    __shared__ double rs[rl];
+    const double rv = threadIdx.x < rl ? w.rec[threadIdx.x] : 0.0;
+    block_sum_partials<K>(w.part, G, sums);
+    if (threadIdx.x < rl) rs[threadIdx.x] = rv;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const double n = (double)d.n_single;
+    const double* al = rs + rec_S(M);
+    const double* ga = rs + rec_S(M) + M;
+    const double last = rs[rec_S(M) + 2 * M];
+    const double* de = rs + rec_lam(M);
+    double A[N][N], z[N], step[M];   // A: lower triangle, A[k][j] = G_jk
+#pragma unroll
+    for (int k = 0; k < M; ++k) step[k] = recip(ga[k]);
+    A[0][0] = n;
+#pragma unroll
+    for (int k = 1; k <= M; ++k) A[k][0] = sums[k - 1];
+#pragma unroll
+    for (int j = 1; j <= M; ++j) A[M][j] = sums[M + j - 1];
+#pragma unroll
+    for (int j = 0; j + 1 < M; ++j) {
+#pragma unroll
+        for (int k = j + 1; k < M; ++k) {
+            const double v = fma(ga[k], A[k + 1][j] + A[k - 1][j], (al[k] - al[j]) * A[k][j]) * step[j];
+            A[k][j + 1] = j > 0 ? v - A[k][j > 0 ? j - 1 : 0] : v;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k <= M; ++k) z[k] = sums[2 * M + k];
+    const double E = sums[K - 1];
+    bool ok = isfinite(E);
+    double be_min = INFINITY, be_max = 0.0;
+#pragma unroll
+    for (int k = 1; k < M; ++k) {
+        be_min = fmin(be_min, ga[k] * ga[k - 1]);
+        be_max = fmax(be_max, ga[k] * ga[k - 1]);
+    }
+    if (M > 2) ok = ok && be_max <= 256.0 * be_min;
+    // A = L D L^T in place (unit L below the diagonal), z = L^-1 P^T r
+    double expect = n, lead = 1.0, dmax = 0.0, dmin = INFINITY, taken = 0.0;
+    double inv[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double dk = A[k][k];
+        if (k > 0) {   // |p_k|^2 / |p_(k-1)|^2 and the leading coefficient 1 / (ga_0 .. ga_(k-1))
+            expect *= k < M ? ga[k < M ? k : 0] * step[k - 1] : last;
+            lead *= ga[k - 1];
+        }
+        ok = ok && isfinite(z[k]) && dk >= 0.015625 * expect && dk <= 64.0 * expect;
+        dmax = fmax(dmax, dk * lead * lead);
+        dmin = fmin(dmin, dk * lead * lead);
+        inv[k] = recip(dk);
+        taken = fma(z[k] * inv[k], z[k], taken);
+        double l[N];
+#pragma unroll
+        for (int i = k + 1; i < N; ++i) l[i] = A[i][k] * inv[k];
+#pragma unroll
+        for (int i = k + 1; i < N; ++i) {
+#pragma unroll
+            for (int j = k + 1; j <= i; ++j) A[i][j] = fma(-l[i], A[j][k], A[i][j]);
+            z[i] = fma(-l[i], z[k], z[i]);
+        }
+#pragma unroll
+        for (int i = k + 1; i < N; ++i) A[i][k] = l[i];
+    }
+    ok = ok && dmin > ldexp(dmax, -72) && (taken <= 0.984375 * E);
+    double g[N];
+#pragma unroll
+    for (int i = N - 1; i >= 0; --i) {
+        double a = z[i] * inv[i];
+#pragma unroll
+        for (int k = i + 1; k < N; ++k) a = fma(-A[k][i], g[k], a);
+        g[i] = a;
+    }
+    // sum_k (de_k + g_k) p_k in powers of t, from the recurrence
+    double b[N], p[N], pp[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        p[j] = j == 0 ? 1.0 : 0.0;
+        pp[j] = 0.0;
+        b[j] = 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double a = de[k] + g[k];
+#pragma unroll
+        for (int j = 0; j <= k; ++j) b[j] = fma(a, p[j], b[j]);
+        if (k < M) {
+            double pn[N];
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const double up = j > 0 ? p[j - 1] : 0.0;
+                pn[j] = fma(fma(-al[k < M ? k : 0], p[j], up), step[k < M ? k : 0], -pp[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                pp[j] = p[j];
+                p[j] = pn[j];
+            }
+        }
+    }
+    const double c = rs[0], s = rs[1];
+    double a[N];
+    to_x_basis<N>(b, c, s, a);
+#pragma unroll
+    for (int k = 0; k < N; ++k) ok = ok && isfinite(a[k]) && isfinite(b[k]);
+    w.tile_start[0] = ok ? 0 : 1;
+    w.tile_start[1] = 0;
+    if (!ok) return;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        coef[k] = a[k];
+        coef[N + k] = b[k];
+        w.rec[rec_b(M) + k] = b[k];
+    }
+    w.pstatus[0] = LSEFIT_OK;
+    status[0] = LSEFIT_OK;
+    if (info) {
+        info[0] = c;
+        info[1] = s;
+        info[2] = E - taken;
     }
 }
 
@@ -440,6 +831,46 @@ hipError_t launch_qr_single(const FitDesc& d, const Work& w, int dtype, const vo
         else
             launch_timed((k_qr_single<double, 1, M>), grid, block, st, d, w, (const double*)x,
                                (const double*)y, L.waves, mis, ra);
+    };
+    dispatch_degree<LSEFIT_MAX_DEGREE>(d.degree, body);
+    return hipGetLastError();
+}
+
+hipError_t launch_qr_sampled(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y,
+                             const Launch& L, int mis, const RangeArg& ra, hipStream_t st) {
+    const dim3 grid(L.waves / L.wpb), block(L.wpb * kWave);
+    auto body = [&]<int M>() {
+        if (dtype == LSEFIT_F32)
+            launch_timed((k_qr_sampled<float, 2, M>), grid, block, st, d, w, (const float*)x, (const float*)y, L.waves,
+                         mis, ra);
+        else
+            launch_timed((k_qr_sampled<double, 2, M>), grid, block, st, d, w, (const double*)x, (const double*)y,
+                         L.waves, mis, ra);
+    };
+    dispatch_degree<LSEFIT_MAX_DEGREE>(d.degree, body);
+    return hipGetLastError();
+}
+
+hipError_t launch_qr_sampled_finish(const FitDesc& d, const Work& w, int64_t G, double* coef, int32_t* status,
+                                    double* info, hipStream_t st) {
+    auto body = [&]<int M>() {
+        launch_timed(k_qr_sampled_finish<M>, dim3(1), dim3(kFinishWaves * kWave), st, d, w, G, coef, status, info);
+    };
+    dispatch_degree<LSEFIT_MAX_DEGREE>(d.degree, body);
+    return hipGetLastError();
+}
+
+hipError_t launch_qr_if_left(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y,
+                             const Launch& L, int mis, const RangeArg& ra, double* coef, int32_t* status,
+                             double* info, hipStream_t st) {
+    const dim3 grid(L.waves / L.wpb), block(L.wpb * kWave);
+    auto body = [&]<int M>() {
+        if (dtype == LSEFIT_F32)
+            hipLaunchKernelGGL((k_qr_if_left<float, 1, M>), grid, block, 0, st, d, w, (const float*)x, (const float*)y,
+                               L.waves, mis, ra, coef, status, info);
+        else
+            hipLaunchKernelGGL((k_qr_if_left<double, 1, M>), grid, block, 0, st, d, w, (const double*)x,
+                               (const double*)y, L.waves, mis, ra, coef, status, info);
     };
     dispatch_degree<LSEFIT_MAX_DEGREE>(d.degree, body);
     return hipGetLastError();
