@@ -1183,6 +1183,55 @@ __device__ inline void adjoint_segment(const PT& P, const In* __restrict__ x, co
     }
 }
 
+// the same for one short fit's points [lo, lo + n) by kGroup lanes (stream_group's
+// pattern: loads and stores of 16 bytes at the alignment of one element, a
+// lane past the fit's vectors reads the last one again and stores nothing)
+template <int U, typename In, class PT>
+__device__ inline void adjoint_group(const PT& P, const In* __restrict__ x, const In* __restrict__ y,
+                                     In* __restrict__ gx, In* __restrict__ gy, int64_t lo, int n) {
+    constexpr int VW = VecOf<In>::W;
+    using V = typename VecOf<In>::type;
+    using VA = typename VecAny<In>::type;
+    const int gl = lane_id() % kGroup;
+    const int nv = n / VW, tail = n - nv * VW;
+    const In* px = x + lo;
+    const In* py = y + lo;
+    In* qx = gx + lo;
+    In* qy = gy + lo;
+    const int last = nv * VW + gl;
+    In tx = 0, ty = 0;
+    if (gl < tail) {
+        tx = px[last];
+        ty = py[last];
+    }
+    for (int j = gl; j < nv; j += kGroup * U) {
+        V xs[U], ys[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(j + u * kGroup, nv - 1) * VW;
+            xs[u] = *reinterpret_cast<const VA*>(px + i);
+            ys[u] = *reinterpret_cast<const VA*>(py + i);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = (j + u * kGroup) * VW;
+            V ox, oy;
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                In gxe, gye;
+                P.point((double)xs[u][e], (double)ys[u][e], gxe, gye);
+                ox[e] = gxe;
+                oy[e] = gye;
+            }
+            if (j + u * kGroup < nv) {
+                *reinterpret_cast<VA*>(qx + i) = ox;
+                *reinterpret_cast<VA*>(qy + i) = oy;
+            }
+        }
+    }
+    if (gl < tail) P.point((double)tx, (double)ty, qx[last], qy[last]);
+}
+
 // fits whose status is not OK get NaN gradients (the block's lanes take turns)
 template <typename In>
 __device__ inline void adjoint_nan(In* __restrict__ gx, In* __restrict__ gy, int64_t lo, int64_t hi, int64_t first,
@@ -1254,17 +1303,25 @@ __device__ inline void adjoint_lambda(int solver, const AdjMeta<MAXM, true>& m, 
 
 // The adjoint pass has no per-wave partial sums, so its tiles go to blocks, not
 // waves: block k takes tiles floor(k NT / K) .. floor((k+1) NT / K) - 1 of the
-// forward's tile table (K blocks) and streams each fit inside that range as
-// one segment, its waves together (adjoint_segment).  The next fit's record is
-// loaded before the current segment is streamed.
+// forward's tile table (K blocks).  The block's waves look at 64 consecutive
+// fits together, a lane each, and sort them into short ones (the rule of
+// walk_grouped, over the 8 fits of a group) and the others.  The waves take
+// turns over the groups with short fits, 8 lanes to a fit; the others are
+// streamed one at a time by all the waves together (adjoint_segment), the next
+// one's record loaded before the current one is streamed.
+// Measured, 60,000 fits of 64 float32 points (61 MB moved): 105 us one fit at a
+// time, 17 us grouped; 4,096 fits of 4,096 points: 45 us either way.
 //
 // SOLVE: no separate solve launch before this one -- the walk loads dL/da and
 // the power sums with the record and solves for lambda itself when the fit's
-// turn comes (every block that streams part of the fit, with the same
+// turn comes (every wave that streams part of the fit, with the same
 // operations, so the same bits); the block that holds the fit's first tile
 // writes lambda to the record.
+// the launch shape's 16 waves per compute unit (adjoint_schedule) need 128 VGPRs
+constexpr int adjoint_waves_per_eu(int U) { return U == 1 ? 4 : 1; }
+
 template <int MAXM, typename In, int U, bool SOLVE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adjoint_waves_per_eu(U))))
     k_adjoint_stream(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, In* __restrict__ gx,
                      In* __restrict__ gy, int64_t W, int mis, int solver, const double* __restrict__ gcoef,
                      int32_t coef_stride) {
@@ -1276,46 +1333,107 @@ __global__ void __launch_bounds__(256)
     const int64_t t0 = (int64_t)blockIdx.x * NT / K;
     const int64_t t1 = ((int64_t)blockIdx.x + 1) * NT / K;
     if (t0 >= t1) return;
-    const int64_t first = (int64_t)wave_id_in_block() * kWave + lane_id();
-    const int64_t step = (int64_t)(blockDim.x / kWave) * kWave;
-    const bool edge = wave_id_in_block() == 0;
-    int64_t f = find_fit(w.tile_start, d.batch, t0);
-    AdjMeta<MAXM, SOLVE> cur = load_adj_meta<MAXM, SOLVE>(d, w, f, gcoef, coef_stride);
-    int64_t t = t0;
-    while (t < t1) {
-        if (cur.fe <= t) {   // a fit without tiles
-            ++f;
-            cur = load_adj_meta<MAXM, SOLVE>(d, w, f, gcoef, coef_stride);
-            continue;
-        }
-        const int64_t te = cur.fe < t1 ? cur.fe : t1;
-        const bool more = te < t1;   // then fit f + 1 < B holds the next tile
-        AdjMeta<MAXM, SOLVE> nxt = cur;
-        if (more) nxt = load_adj_meta<MAXM, SOLVE>(d, w, f + 1, gcoef, coef_stride);
-        const int64_t plo = cur.lo + (t - cur.fs) * tile;
-        int64_t phi = cur.lo + (te - cur.fs) * tile;
-        if (phi > cur.hi) phi = cur.hi;
-        if (cur.st != LSEFIT_OK) {
-            adjoint_nan(gx, gy, plo, phi, first, step);
-        } else {
-            auto body = [&]<int M>() {
-                if constexpr (SOLVE) {
-                    adjoint_lambda<M, MAXM>(solver, cur, cur.lam);
-                    if (t == cur.fs && threadIdx.x == 0) {
-                        double* r = w.rec + f * rec_len(MAXM);
+    const int wid = wave_id_in_block(), nw = blockDim.x / kWave, lane = lane_id();
+    const int64_t first = (int64_t)wid * kWave + lane;
+    const int64_t step = (int64_t)nw * kWave;
+    constexpr int kU = 2, kRound = 16 * kGroup * kU;   // fewer vectors in flight than the forward: stores as well
+    const int64_t f00 = find_fit(w.tile_start, d.batch, t0);
+    // of the 64 fits from f0 on, those to be streamed one at a time and the short
+    // ones; more: fit f0 + 64 < B holds the next tile
+    auto sort_fits = [&](int64_t f0, uint64_t& one, uint64_t& shorts, bool& more) {
+        const int64_t fl = f0 + lane < d.batch ? f0 + lane : d.batch - 1;   // past the last fit: the last, dropped
+        const int64_t fs = w.tile_start[fl], fe = w.tile_start[fl + 1];
+        const int64_t bytes = (fit_hi(d, fl) - fit_lo(d, fl)) * (int)sizeof(In);
+        const int st = w.pstatus[fl];
+        const bool in = f0 + lane < d.batch && fs < t1 && fe > t0 && fs < fe;
+        const bool could = in && fs >= t0 && fe <= t1 && bytes <= kGroups * kRound && st == LSEFIT_OK;
+        const int c = __popcll((__ballot(could) >> (lane / kGroups * kGroups)) & ((1ull << kGroups) - 1));
+        const bool mine = could && bytes <= c * kRound;
+        shorts = __ballot(mine);
+        one = __ballot(in && !mine);
+        more = bcast_i64(fe, kWave - 1) < t1;
+    };
+    bool more = true, any = false;
+    for (int64_t f0 = f00; more; f0 += kWave) {
+        // the first fit's record comes with the 64 fits' own lines: it is usually
+        // the first to be streamed
+        AdjMeta<MAXM, SOLVE> cur = load_adj_meta<MAXM, SOLVE>(d, w, f0, gcoef, coef_stride);
+        uint64_t todo, shorts;
+        sort_fits(f0, todo, shorts, more);
+        any = any || shorts != 0;
+        int at = todo ? __ffsll((unsigned long long)todo) - 1 : 0;
+        if (todo && at) cur = load_adj_meta<MAXM, SOLVE>(d, w, f0 + at, gcoef, coef_stride);
+        while (todo) {
+            todo &= todo - 1;
+            const int64_t f = f0 + at;
+            AdjMeta<MAXM, SOLVE> nxt = cur;
+            if (todo) {
+                at = __ffsll((unsigned long long)todo) - 1;
+                nxt = load_adj_meta<MAXM, SOLVE>(d, w, f0 + at, gcoef, coef_stride);
+            }
+            const int64_t tb = cur.fs > t0 ? cur.fs : t0, te = cur.fe < t1 ? cur.fe : t1;
+            const int64_t plo = cur.lo + (tb - cur.fs) * tile;
+            int64_t phi = cur.lo + (te - cur.fs) * tile;
+            if (phi > cur.hi) phi = cur.hi;
+            if (cur.st != LSEFIT_OK) {
+                adjoint_nan(gx, gy, plo, phi, first, step);
+            } else {
+                auto body = [&]<int M>() {
+                    if constexpr (SOLVE) {
+                        adjoint_lambda<M, MAXM>(solver, cur, cur.lam);
+                        if (tb == cur.fs && threadIdx.x == 0) {
+                            double* r = w.rec + f * rec_len(MAXM);
 #pragma unroll
-                        for (int k = 0; k <= M; ++k) r[rec_lam(MAXM) + k] = cur.lam[k];
+                            for (int k = 0; k <= M; ++k) r[rec_lam(MAXM) + k] = cur.lam[k];
+                        }
                     }
-                }
-                AdjointPoint<M, In> P;
-                P.template init<MAXM>(cur.c, cur.s, cur.b, cur.lam);
-                adjoint_segment<U>(P, x, y, gx, gy, plo, phi, mis, first, step, edge);
-            };
-            dispatch_degree<MAXM>(cur.deg, body);
+                    AdjointPoint<M, In> P;
+                    P.template init<MAXM>(cur.c, cur.s, cur.b, cur.lam);
+                    adjoint_segment<U>(P, x, y, gx, gy, plo, phi, mis, first, step, wid == 0);
+                };
+                dispatch_degree<MAXM>(cur.deg, body);
+            }
+            cur = nxt;
         }
-        t = te;
-        ++f;
-        cur = nxt;
+    }
+    if (!any) return;
+    // the short fits in a loop of their own, so that neither loop holds the
+    // other's registers
+    int turn = 0;
+    more = true;
+    for (int64_t f0 = f00; more; f0 += kWave) {
+        uint64_t one, shorts;
+        sort_fits(f0, one, shorts, more);
+        for (int g8 = 0; g8 < kWave; g8 += kGroups) {
+            if (!((shorts >> g8) & ((1ull << kGroups) - 1)) || turn++ % nw != wid) continue;
+            const int k8 = g8 + lane / kGroup;   // this lane's fit
+            const bool own = (shorts >> k8) & 1;
+            const int64_t f = f0 + k8 < d.batch ? f0 + k8 : d.batch - 1;
+            const AdjMeta<MAXM, SOLVE> m = load_adj_meta<MAXM, SOLVE>(d, w, f, gcoef, coef_stride);
+            double lam[MAXM + 1], b[MAXM + 1];
+            if constexpr (SOLVE) {
+#pragma unroll
+                for (int k = 0; k <= MAXM; ++k) lam[k] = 0.0;
+                if (own) {
+                    dispatch_degree<MAXM>(m.deg, [&]<int M>() {
+                        adjoint_lambda<M, MAXM>(solver, m, lam);
+                        if (lane % kGroup == 0) {
+                            double* r = w.rec + f * rec_len(MAXM);
+#pragma unroll
+                            for (int k = 0; k <= M; ++k) r[rec_lam(MAXM) + k] = lam[k];
+                        }
+                    });
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k <= MAXM; ++k) lam[k] = k <= m.deg ? m.lam[k] : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k <= MAXM; ++k) b[k] = k <= m.deg ? m.b[k] : 0.0;
+            AdjointPoint<MAXM, In> P;   // the entries past the fit's degree are 0: the same values
+            P.template init<MAXM>(m.c, m.s, b, lam);
+            adjoint_group<kU>(P, x, y, gx, gy, m.lo, own ? (int)(m.hi - m.lo) : 0);
+        }
     }
 }
 

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from gpu_common import announce, normwise, to_dev, torch
-from oracle import fp64
+from oracle import adjoint, fp64
 from paper_1512_08017_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +84,44 @@ def test_short_fits_compensated():
         assert e <= 1e-6, (f, hi - lo, m, e)
         done += 1
     assert done > 100
+
+
+@pytest.mark.parametrize("dtype,maxdeg,count,shift,solver", [(np.float32, 2, 8, 0, "gepp"), (np.float64, 3, 7, 1, "gepp"),
+                                                             (np.float32, 3, 1, 2, "cholesky"),
+                                                             (np.float64, 5, 9, 0, "gepp"), (np.float32, 1, 15, 1, "gepp")])
+def test_short_fits_backward(dtype, maxdeg, count, shift, solver):
+    """dL/dx and dL/dy of the same batches (solve in the walk up to degree 3, in its own
+    launch above) against the closed form, each fit normwise.  Both sides solve with the
+    same matrix; lambda and b carry cond(A) roundings, then the type's own."""
+    announce(f"short fits backward {np.dtype(dtype).name} degree <= {maxdeg} count {count} shift {shift} {solver}")
+    n = lengths(count, 70 + maxdeg)
+    rng = np.random.default_rng(count + 100)
+    deg = rng.integers(1, maxdeg + 1, n.size).astype(np.int32)
+    bf = W.random_batch(n, deg, seed=71 + maxdeg, dtype=dtype)
+    pad = np.zeros(2, dtype)
+    x = to_dev(np.concatenate([pad[:shift], bf.x]))[shift:]
+    y = to_dev(np.concatenate([pad[:1 if shift else 0], bf.y]))[1 if shift else 0:]
+    off, dg = to_dev(bf.offsets), to_dev(bf.degrees)
+    gbar = rng.standard_normal((n.size, maxdeg + 1))
+    kw = dict(center=0.0, scale=1.0, solver=solver)
+    _, status, ws = lf.fit_batched(x, y, off, dg, maxdeg, **kw)
+    gx, gy = lf.fit_backward(x, y, off, dg, maxdeg, to_dev(gbar), ws=ws, **kw)
+    torch.cuda.synchronize()
+    gx, gy, status = gx.cpu().numpy(), gy.cpu().numpy(), status.cpu().numpy()
+    assert gx.shape == bf.x.shape
+    for f in range(bf.batch):
+        m, lo, hi = int(deg[f]), bf.offsets[f], bf.offsets[f + 1]
+        if hi - lo < m + 1:
+            assert status[f] == 2 and np.isnan(gx[lo:hi]).all() and np.isnan(gy[lo:hi]).all()
+            continue
+        tol = gate(bf.x[lo:hi], m, 0.0, 1.0) + 2.0 * float(np.finfo(dtype).eps)
+        if tol > 1e-3:
+            continue
+        ref = adjoint.gradients(bf.x[lo:hi], bf.y[lo:hi], m, gbar[f, : m + 1])
+        # dL/dx = q' r - q f': gated against the size of its two terms
+        t = bf.x[lo:hi].astype(np.float64)
+        poly, r = np.polynomial.polynomial, bf.y[lo:hi] - np.polynomial.polynomial.polyval(t, ref["b"])
+        size = np.max(np.abs(poly.polyval(t, poly.polyder(ref["lam"])) * r)) + np.max(
+            np.abs(ref["dy"] * poly.polyval(t, poly.polyder(ref["b"]))))
+        assert np.max(np.abs(gx[lo:hi] - ref["dx"])) <= tol * size, (f, hi - lo, m)
+        assert np.max(np.abs(gy[lo:hi] - ref["dy"])) <= tol * np.max(np.abs(ref["dy"])), (f, hi - lo, m)
