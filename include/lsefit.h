@@ -224,7 +224,9 @@ lsefit_status fit_solve(const double* moments, const lsefit_options* opt,
 
 /* fit_moments followed by fit_solve in one call, with fewer launches: the
  * kernel that sums the per-block partial sums also solves (two launches for
- * LSEFIT_PREC_F64; two more for the refinement pass of LSEFIT_PREC_F32C).
+ * LSEFIT_PREC_F64; two more for the refinement pass of LSEFIT_PREC_F32C).  Up to
+ * 16,384 points (monomial basis, initial default schedule) the first two are
+ * one launch of one block, for fit_moments too.
  *  coef:     output, device float64 [2(m+1)]: a_0..a_m (x-basis), b_0..b_m (t-basis)
  *  status:   output, device int32 [1]
  *  moments:  optional output (NULL to skip), device float64 [3m+4] as in fit_moments
@@ -451,7 +453,7 @@ lsefit_status lsefit_copy_probe(const float* x, const float* y, float* ox, float
  *        fit_qr's two routes the first one tried),
  *        1 = refinement pass, 2 = adjoint streaming pass (not its per-fit
  *        solve), 3 = per-fit combine and solve (the finish kernel of a single
- *        fit), 4 = read or copy probe, 5 = residual pass (not its per-fit
+ *        fit; a small fit's one launch counts as kind 0), 4 = read or copy probe, 5 = residual pass (not its per-fit
  *        fold), 6 = range pass (Chebyshev basis, automatic range; not its
  *        per-fit fold), 7 = tile table of a batch (its first launch: the
  *        whole table when the batch has at most 32 blocks of 256 fits and a

@@ -151,6 +151,21 @@ lsefit_schedule single_schedule(int64_t n, int dt, const lsefit_options* o) {
     return s;
 }
 
+// Up to this many points a single power-basis fit takes one launch of one block
+// (k_fit_small) while the default schedule is the initial one.  The streaming grid's
+// two launches cost more than the points there: 4,097 float64 points, m = 3, 9.0
+// us of GPU time in two launches and 6.2 in one (the call 11.2 and 8.0 us, the
+// host's launches); 16,000 float32 points 9.2 and 7.7 us at m = 3, 16.3 and 15.1 at
+// m = 8.  One compute unit adds about 0.15 us per 1,000 points, so the lines cross
+// near 24,000.
+constexpr int64_t kOneBlockPoints = 1 << 14;
+
+bool one_block(int64_t n) {
+    bool user = false;
+    (void)current_default(&user);
+    return !user && n <= kOneBlockPoints;
+}
+
 bool schedule_ok(const lsefit_schedule& s) {
     const int wpb = s.waves_per_block;
     return s.waves >= 1 && s.waves <= (1 << 22) && (wpb == 1 || wpb == 2 || wpb == 4) && s.tile >= 64 &&
@@ -494,6 +509,12 @@ lsefit_status single_pass(bool refine_pass, const FitDesc& d, const Work& w, con
                          [&] { return launch_moments_cheb(d, w, opt->degree, dt, x, y, L, mis, rc, st); }));
         LSEFIT_TRY(timed(kTimeCombine, st,
                          [&] { return launch_finish_cheb(d, w, opt->degree, grid_blocks(L), fz, st); }));
+        return LSEFIT_OK;
+    }
+    if (!refine_pass && one_block(d.n_single)) {
+        LSEFIT_TRY(timed(kTimeMoments, st, [&] {
+            return launch_fit_small(d, w, opt->degree, opt->precision, dt, x, y, mis, ra, fz, st);
+        }));
         return LSEFIT_OK;
     }
     if (refine_pass)

@@ -363,6 +363,11 @@ hipError_t launch_moments(const FitDesc& d, const Work& w, int maxM, int prec, i
     LSEFIT_SWITCH_MAXM(maxM, return Launchers<MM>::moments(d, w, prec, dtype, x, y, L, mis, ra, st));
 }
 
+hipError_t launch_fit_small(const FitDesc& d, const Work& w, int maxM, int prec, int dtype, const void* x,
+                            const void* y, int mis, const RangeArg& ra, const Finish& fz, hipStream_t st) {
+    LSEFIT_SWITCH_MAXM(maxM, return Launchers<MM>::fit_small(d, w, prec, dtype, x, y, mis, ra, fz, st));
+}
+
 hipError_t launch_finish_single(const FitDesc& d, const Work& w, int maxM, int64_t blocks, const Finish& fz,
                                 hipStream_t st) {
     LSEFIT_SWITCH_MAXM(maxM, return Launchers<MM>::finish_single(d, w, blocks, fz, st));

@@ -90,6 +90,10 @@ hipError_t launch_plan(const FitDesc& d, const Work& w, int maxM, int64_t tile, 
 hipError_t launch_moments(const FitDesc& d, const Work& w, int maxM, int prec, int dtype, const void* x,
                           const void* y, const Launch& L, int mis, const RangeArg& ra, hipStream_t st);
 
+// A small single fit in one launch of one block: range, power sums and finish.
+hipError_t launch_fit_small(const FitDesc& d, const Work& w, int maxM, int prec, int dtype, const void* x,
+                            const void* y, int mis, const RangeArg& ra, const Finish& fz, hipStream_t st);
+
 // Single fit: sum the block partials and finish (mode of fz).
 hipError_t launch_finish_single(const FitDesc& d, const Work& w, int maxM, int64_t blocks, const Finish& fz,
                                 hipStream_t st);

@@ -910,6 +910,78 @@ __global__ void __launch_bounds__(256)
     });
 }
 
+// ---------------------------------------------------------------------------
+// a small single fit in one launch: one block of kSmallWaves waves derives the
+// range, sums all the points and finishes the fit.  Bound by its chain of memory
+// round trips, wave sums and the solve (4,097 float64 points, m = 3: 5.3 us by
+// its clock, of which the solve and the stores take about 2.5).
+// ---------------------------------------------------------------------------
+constexpr int kSmallWaves = 8;
+
+// (c, s) from the samples of single_range, by one wave (exact extremes: the
+// same bits)
+template <typename In>
+__device__ inline void wave_range(const In* __restrict__ x, int64_t n, const RangeArg& ra, double* c, double* s) {
+    *c = ra.c;
+    *s = ra.s;
+    if (ra.mode != LSEFIT_RANGE_AUTO) return;
+    constexpr int J = kSingleRangeSamples / kWave;
+    double v[J], lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = lane_id() + j * kWave;
+        v[j] = (double)x[n > kSingleRangeSamples ? sample_at(i, n) : (i < n ? (int64_t)i : n - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        if (isfinite(v[j])) {
+            lo = fmin(lo, v[j]);
+            hi = fmax(hi, v[j]);
+        }
+    }
+    snap_range(wave_min(lo), wave_max(hi), c, s);
+}
+
+template <int M, int PREC, typename In>
+__global__ void __launch_bounds__(kSmallWaves * kWave)
+    k_fit_small(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int mis, RangeArg ra, Finish fz) {
+    const KernelClock kclock_(w.clock);
+    using Acc = std::conditional_t<PREC == LSEFIT_PREC_F64, AccF64<M>, AccF32C<M>>;
+    constexpr int K = nacc(M);
+    __shared__ double sh[kSmallWaves][K];
+    __shared__ double sm[3 * M + 2];
+    __shared__ double rs[2];
+    const int wid = wave_id_in_block();
+    Acc acc;
+    double c, s;
+    // every wave takes the range from the samples while its first loads are in flight
+    stream_strided<2, true>(x, y, d.n_single, mis, wid, kSmallWaves, acc, [&] {
+        wave_range(x, d.n_single, ra, &c, &s);
+        acc.init(c, 1.0 / s);
+    });
+    double v[K];
+    acc.out(v);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    if (lane_id() == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) sh[wid][k] = v[k];
+    }
+    if (threadIdx.x == 0) {
+        w.rec[0] = rs[0] = c;
+        w.rec[1] = rs[1] = s;
+        w.pstatus[0] = LSEFIT_OK;
+    }
+    __syncthreads();
+    if (wid != 0) return;
+    wave_column_sums<K, K>(sh, kSmallWaves, v);
+    if constexpr (M <= kFinishLaneMax) {
+        if (lane_id() == 0) finish_fit<M, M>(d, w, 0, v, fz, d.n_single, c, s, nullptr);
+    } else {
+        finish_fit_wave<M, M>(d, w, 0, v, fz, sm, rs);
+    }
+}
+
 template <int MAXM, typename In, int U>
 __global__ void __launch_bounds__(256)
     k_refine(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W,
@@ -1589,6 +1661,22 @@ hipError_t Launchers<MAXM>::moments(const FitDesc& d, const Work& w, int prec, i
     if (prec == LSEFIT_PREC_F32C && dtype == LSEFIT_F32)
         return moments_t<LSEFIT_PREC_F32C, float>(d, w, x, y, L, mis, ra, st);
     return hipErrorInvalidValue;
+}
+
+template <int MAXM>
+hipError_t Launchers<MAXM>::fit_small(const FitDesc& d, const Work& w, int prec, int dtype, const void* x,
+                                      const void* y, int mis, const RangeArg& ra, const Finish& fz, hipStream_t st) {
+    const dim3 grid(1), block(kSmallWaves * kWave);
+    if (prec == LSEFIT_PREC_F64 && dtype == LSEFIT_F64)
+        launch_timed((k_fit_small<MAXM, LSEFIT_PREC_F64, double>), grid, block, st, d, w, (const double*)x,
+                     (const double*)y, mis, ra, fz);
+    else if (prec == LSEFIT_PREC_F64)
+        launch_timed((k_fit_small<MAXM, LSEFIT_PREC_F64, float>), grid, block, st, d, w, (const float*)x,
+                     (const float*)y, mis, ra, fz);
+    else
+        launch_timed((k_fit_small<MAXM, LSEFIT_PREC_F32C, float>), grid, block, st, d, w, (const float*)x,
+                     (const float*)y, mis, ra, fz);
+    return hipGetLastError();
 }
 
 template <int MAXM>

@@ -10,6 +10,8 @@ template <int MAXM>
 struct Launchers {
     static hipError_t moments(const FitDesc& d, const Work& w, int prec, int dtype, const void* x, const void* y,
                               const Launch& L, int mis, const RangeArg& ra, hipStream_t st);
+    static hipError_t fit_small(const FitDesc& d, const Work& w, int prec, int dtype, const void* x, const void* y,
+                                int mis, const RangeArg& ra, const Finish& fz, hipStream_t st);
     static hipError_t finish_single(const FitDesc& d, const Work& w, int64_t G, const Finish& fz, hipStream_t st);
     static hipError_t combine(const FitDesc& d, const Work& w, const Launch& L, bool by_block, const Finish& fz,
                               hipStream_t st);
