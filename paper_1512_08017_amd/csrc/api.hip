@@ -55,7 +55,8 @@ Layout layout(int64_t B, int maxM, int64_t W) {
     L.part = off;
     // the slots may also hold streaming QR factors (fit_qr, degree <= LSEFIT_MAX_DEGREE)
     const int per = (maxM <= LSEFIT_MAX_DEGREE && qr_len(maxM) > nacc(maxM)) ? qr_len(maxM) : nacc(maxM);
-    off = align_up(off + sizeof(double) * (size_t)(W + B) * per);
+    // (and, after a single fit's sums, the block pairs of the Chebyshev range pass)
+    off = align_up(off + sizeof(double) * ((size_t)(W + B) * per + 2 * (size_t)W));
     L.block_tot = off;
     off = align_up(off + sizeof(int64_t) * (size_t)((B + kPlanThreads - 1) / kPlanThreads));
     L.total = off + kAlign;   // slack for aligning the caller's base pointer
@@ -503,7 +504,7 @@ lsefit_status single_pass(bool refine_pass, const FitDesc& d, const Work& w, con
         if (opt->range_mode == LSEFIT_RANGE_AUTO) {
             LSEFIT_TRY(timed(kTimeRange, st,
                              [&] { return launch_range_cheb(d, w, opt->degree, dt, x, L, mis, st); }));
-            rc.mode = kRangeFromRecord;
+            rc.mode = kRangeFromPairs;
         }
         LSEFIT_TRY(timed(kTimeMoments, st,
                          [&] { return launch_moments_cheb(d, w, opt->degree, dt, x, y, L, mis, rc, st); }));

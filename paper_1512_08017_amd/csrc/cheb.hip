@@ -97,7 +97,8 @@ struct MinMax {
     }
 };
 
-// x only, the sweep of the single-fit streaming pass (grid stride over 16-byte vectors)
+// x only, the sweep of the single-fit streaming pass (grid stride over 16-byte
+// vectors), the next round's U vectors loaded before the current ones are folded
 template <typename In>
 __device__ inline void minmax_strided(const In* __restrict__ x, int64_t n, int mis, int64_t gwave, int64_t W,
                                       MinMax<In>& r) {
@@ -113,13 +114,29 @@ __device__ inline void minmax_strided(const In* __restrict__ x, int64_t n, int m
         const int64_t b = a + nv * VW;
         if (gwave == 0 && lane < a) r.add(ld_scalar(x + lane));
         const V* __restrict__ xv = reinterpret_cast<const V*>(x + a);
+        const int64_t span = (int64_t)(U - 1) * step, round = (int64_t)U * step;
         int64_t j = gwave * kWave + lane;
-        for (; j + (int64_t)(U - 1) * step < nv; j += (int64_t)U * step) {
-            V v[U];
+        bool have = j + span < nv;
+        V v[U];
+        if (have) {
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = ld_stream(xv + j + u * step);
+        }
+        while (have) {
+            const bool next = j + round + span < nv;
+            V q[U];
+            if (next) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) q[u] = ld_stream(xv + j + round + u * step);
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u) r.template vec<V, VW>(v[u]);
+            if (next) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = q[u];
+            }
+            j += round;
+            have = next;
         }
         for (; j < nv; j += step) r.template vec<V, VW>(ld_stream(xv + j));
         if (gwave == 0 && lane < n - b) r.add(ld_scalar(x + b + lane));
@@ -159,10 +176,15 @@ __device__ inline void minmax_segment(const In* __restrict__ x, int64_t lo, int6
     }
 }
 
-// single fit: one (min, max) pair per block into part[2 blockIdx.x ..]
+// The block pairs (min, max) of a single fit's range pass, past the K sums per
+// block that the power-sum pass is about to write (the workspace holds both:
+// layout in api.hip), so that every block of that pass can fold them itself
+__device__ inline double* range_pairs(const Work& w, int K, int64_t G) { return w.part + (int64_t)K * G; }
+
+// single fit: one (min, max) pair per block
 template <typename In>
 __global__ void __launch_bounds__(256)
-    k_range_cheb_single(FitDesc d, Work w, const In* __restrict__ x, int64_t W, int mis) {
+    k_range_cheb_single(FitDesc d, Work w, const In* __restrict__ x, int64_t W, int mis, int K) {
     const KernelClock kclock_(w.clock);
     __shared__ double slo[4], shi[4];
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
@@ -180,19 +202,21 @@ __global__ void __launch_bounds__(256)
             a = fmin(a, slo[i]);
             b = fmax(b, shi[i]);
         }
-        w.part[2 * (int64_t)blockIdx.x] = a;
-        w.part[2 * (int64_t)blockIdx.x + 1] = b;
+        double* pairs = range_pairs(w, K, gridDim.x);
+        pairs[2 * (int64_t)blockIdx.x] = a;
+        pairs[2 * (int64_t)blockIdx.x + 1] = b;
     }
 }
 
-// single fit: fold the G block pairs, set (c, s) and the fit's status
-__global__ void __launch_bounds__(256) k_range_fold_single(Work w, int64_t G) {
-    const KernelClock kclock_(w.clock);
+// the G block pairs folded by one block (exact extremes: any split gives the
+// same bits); block 0 records (c, s) and the fit's status
+__device__ inline void range_from_pairs(const Work& w, int K, int64_t G, double* c, double* s) {
     __shared__ double slo[4], shi[4];
+    const double* pairs = range_pairs(w, K, G);
     double lo = INFINITY, hi = -INFINITY;
     for (int64_t g = threadIdx.x; g < G; g += blockDim.x) {
-        lo = fmin(lo, w.part[2 * g]);
-        hi = fmax(hi, w.part[2 * g + 1]);
+        lo = fmin(lo, pairs[2 * g]);
+        hi = fmax(hi, pairs[2 * g + 1]);
     }
     lo = wave_min(lo);
     hi = wave_max(hi);
@@ -201,12 +225,16 @@ __global__ void __launch_bounds__(256) k_range_fold_single(Work w, int64_t G) {
         shi[wave_id_in_block()] = hi;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < (int)(blockDim.x / kWave); ++i) {
-            lo = fmin(lo, slo[i]);
-            hi = fmax(hi, shi[i]);
-        }
-        cheb_range(lo, hi, &w.rec[0], &w.rec[1]);
+    lo = slo[0];
+    hi = shi[0];
+    for (int i = 1; i < (int)(blockDim.x / kWave); ++i) {
+        lo = fmin(lo, slo[i]);
+        hi = fmax(hi, shi[i]);
+    }
+    cheb_range(lo, hi, c, s);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        w.rec[0] = *c;
+        w.rec[1] = *s;
         w.pstatus[0] = LSEFIT_OK;
     }
 }
@@ -355,9 +383,10 @@ __global__ void __launch_bounds__(256)
     const KernelClock kclock_(w.clock);
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
     double c, inv_s;
-    if (ra.mode == kRangeFromRecord) {
-        c = w.rec[0];
-        inv_s = 1.0 / w.rec[1];
+    if (ra.mode == kRangeFromPairs) {
+        double s;
+        range_from_pairs(w, nacc(M), gridDim.x, &c, &s);
+        inv_s = 1.0 / s;
     } else {
         single_range(d, w, x, ra, &c, &inv_s);
     }
@@ -845,10 +874,8 @@ hipError_t range_cheb_typed(const FitDesc& d, const Work& w, int maxm, const In*
                             hipStream_t st) {
     const int64_t G = L.waves / L.wpb;
     if (is_single(d)) {
-        launch_timed((k_range_cheb_single<In>), dim3(G), dim3(L.wpb * kWave), st, d, w, x, L.waves, mis);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        launch_timed(k_range_fold_single, dim3(1), dim3(256), st, w, G);
+        launch_timed((k_range_cheb_single<In>), dim3(G), dim3(L.wpb * kWave), st, d, w, x, L.waves, mis,
+                     nacc(d.degree));
         return hipGetLastError();
     }
     launch_timed((k_range_cheb_batch<In>), dim3(G), dim3(L.wpb * kWave), st, d, w, x, L.waves,

@@ -72,11 +72,11 @@ struct Finish {
 
 // Range of a single fit: given (c, s), or derived by the streaming kernel itself.
 struct RangeArg {
-    int mode;   // lsefit_range_mode, or kRangeFromRecord
+    int mode;   // lsefit_range_mode, or kRangeFromPairs
     double c, s;
 };
-// (c, s) already in the fit's record (written by an earlier range pass)
-constexpr int kRangeFromRecord = 2;
+// (c, s) from the block pairs of the Chebyshev range pass before this one
+constexpr int kRangeFromPairs = 2;
 
 // Batched: tile table, plan status and (c, s) of every fit (given, or from a
 // sample of the fit's x), in two launches (one for at most 32 blocks of fits and
@@ -136,7 +136,7 @@ hipError_t launch_copy_probe(const float* x, const float* y, float* ox, float* o
 // and a solve from caller-provided sums.
 // exact extent of the finite x of every fit -> (c, s) of the Chebyshev basis in
 // its record (a streaming pass over x with per-block / per-slot min and max,
-// then a per-fit fold)
+// then for batches a per-fit fold; a single fit's power-sum pass folds the pairs)
 hipError_t launch_range_cheb(const FitDesc& d, const Work& w, int maxm, int dtype, const void* x, const Launch& L,
                              int mis, hipStream_t st);
 hipError_t launch_moments_cheb(const FitDesc& d, const Work& w, int maxm, int dtype, const void* x, const void* y,
