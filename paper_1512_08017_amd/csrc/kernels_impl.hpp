@@ -1011,9 +1011,30 @@ __global__ void __launch_bounds__(256)
         dispatch_degree<MAXM>(d.degree, body);
         return;
     }
-    walk_segments_ahead(d, w.tile_start, w.pstatus, w.rec, rl, wave, W,
-                        [&](int64_t f, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
-        if (mt.st != LSEFIT_OK) return;
+    // short fits as in the power-sum pass; the coefficients past a fit's degree
+    // are 0, which leaves its residuals as they are
+    auto short_fits = [&](int64_t f, bool mine, const SegMeta& mt) {
+        const double* b = w.rec + (mine ? f : 0) * rl + rec_b(MAXM);
+        double bb[MAXM + 1];
+#pragma unroll
+        for (int j = 0; j <= MAXM; ++j) bb[j] = b[j];
+#pragma unroll
+        for (int j = 0; j <= MAXM; ++j) bb[j] = j <= mt.deg ? bb[j] : 0.0;
+        AccRefine<MAXM> acc;
+        acc.init(mt.c, 1.0 / mt.s, bb);
+        stream_group<kGroupUnroll>(x, y, mt.lo, mine ? (int)(mt.hi - mt.lo) : 0, acc);
+        double v[MAXM + 1];
+#pragma unroll
+        for (int k = 0; k <= MAXM; ++k) v[k] = group8_sum(acc.R[k]);
+        double* __restrict__ out = w.part + (wave + f) * stride;
+        if (mine && lane_id() % kGroup == 0) {
+#pragma unroll
+            for (int k = 0; k <= MAXM; ++k)
+                if (k <= mt.deg) out[k] = v[k];
+        }
+    };
+    walk_grouped(d, w.tile_start, w.pstatus, w.rec, rl, wave, W, (int)sizeof(In), short_fits,
+                 [&](int64_t f, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
         const double* r = w.rec + f * rl;
         const double c = mt.c;
         const double inv_s = 1.0 / mt.s;
