@@ -396,8 +396,8 @@ hipError_t launch_adjoint(const FitDesc& d, const Work& w, int maxM, int solver,
 }
 
 hipError_t launch_residual(const FitDesc& d, const Work& w, int maxM, int dtype, const void* x, const void* y,
-                           void* resid, const Launch& L, int mis, hipStream_t st) {
-    LSEFIT_SWITCH_MAXM(maxM, return Launchers<MM>::residual(d, w, dtype, x, y, resid, L, mis, st));
+                           void* resid, const Launch& L, int mis, bool keep, hipStream_t st) {
+    LSEFIT_SWITCH_MAXM(maxM, return Launchers<MM>::residual(d, w, dtype, x, y, resid, L, mis, keep, st));
 }
 
 }  // namespace lsefit

@@ -119,8 +119,9 @@ hipError_t launch_adjoint(const FitDesc& d, const Work& w, int maxM, int solver,
 
 // Residual pass: e = y - f(t) per point (optionally stored) and partial sums of
 // e^2 (per block for a single fit, per wave and fit for a batch) into w.part.
+// keep (single fit): store e through the cache.
 hipError_t launch_residual(const FitDesc& d, const Work& w, int maxM, int dtype, const void* x, const void* y,
-                           void* resid, const Launch& L, int mis, hipStream_t st);
+                           void* resid, const Launch& L, int mis, bool keep, hipStream_t st);
 
 // Read-bandwidth probe over two float32 arrays of nvec 16-byte vectors each;
 // one float per block into out.

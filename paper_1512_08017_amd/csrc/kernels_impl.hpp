@@ -1554,8 +1554,10 @@ struct ResidPoint {
 };
 
 // one wave: points [lo, hi) of one fit (or the whole grid-stride share of a
-// single fit when `strided`), e^2 summed per lane into acc, e stored if resid
-template <class PT, typename In, bool STRIDED, int U>
+// single fit when `strided`), e^2 summed per lane into acc, e stored if resid;
+// KEEP: with ordinary stores, which the Infinity Cache takes (keep_residuals in
+// api.hip), not non-temporal ones
+template <class PT, typename In, bool STRIDED, int U, bool KEEP = false>
 __device__ inline void resid_points(const In* __restrict__ x, const In* __restrict__ y, In* __restrict__ resid,
                                     int64_t lo, int64_t hi, int mis, int64_t gwave, int64_t W,
                                     const PT& P, double& acc) {
@@ -1587,7 +1589,11 @@ __device__ inline void resid_points(const In* __restrict__ x, const In* __restri
                 acc = fma(er, er, acc);
                 os[e] = (In)er;
             }
-            if (rv) __builtin_nontemporal_store(os, rv + j);
+            if constexpr (KEEP) {
+                if (rv) rv[j] = os;
+            } else {
+                if (rv) __builtin_nontemporal_store(os, rv + j);
+            }
         };
         // U vectors per lane are loaded before any is used (U rounds of loads in flight)
         int64_t j = first;
@@ -1611,7 +1617,7 @@ __device__ inline void resid_points(const In* __restrict__ x, const In* __restri
 template <int MAXM, typename In, int U>
 __global__ void __launch_bounds__(256)
     k_residual(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, In* __restrict__ resid,
-               int64_t W, int mis) {
+               int64_t W, int mis, bool keep) {
     const KernelClock kclock_(w.clock);
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
     constexpr int stride = nacc(MAXM);
@@ -1623,7 +1629,10 @@ __global__ void __launch_bounds__(256)
             if (ok) {
                 ResidPoint<M> P;
                 P.init(w.rec, MAXM);
-                resid_points<ResidPoint<M>, In, true, U>(x, y, resid, 0, d.n_single, mis, wave, W, P, acc);
+                if (keep)
+                    resid_points<ResidPoint<M>, In, true, U, true>(x, y, resid, 0, d.n_single, mis, wave, W, P, acc);
+                else
+                    resid_points<ResidPoint<M>, In, true, U>(x, y, resid, 0, d.n_single, mis, wave, W, P, acc);
             } else if (resid) {
                 for (int64_t i = wave * kWave + lane_id(); i < d.n_single; i += W * kWave) resid[i] = (In)NAN;
             }
@@ -1802,15 +1811,15 @@ hipError_t Launchers<MAXM>::adjoint(const FitDesc& d, const Work& w, int solver,
 
 template <int MAXM>
 hipError_t Launchers<MAXM>::residual(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y,
-                                     void* resid, const Launch& L, int mis, hipStream_t st) {
+                                     void* resid, const Launch& L, int mis, bool keep, hipStream_t st) {
     const dim3 grid(blocks_for(L)), block(L.wpb * kWave);
 #define LSEFIT_RES(UU)                                                                                           \
     if (dtype == LSEFIT_F32)                                                                                     \
         launch_timed((k_residual<MAXM, float, UU>), grid, block, st, d, w, (const float*)x,            \
-                           (const float*)y, (float*)resid, L.waves, mis);                                \
+                           (const float*)y, (float*)resid, L.waves, mis, keep);                                \
     else                                                                                                         \
         launch_timed((k_residual<MAXM, double, UU>), grid, block, st, d, w, (const double*)x,          \
-                           (const double*)y, (double*)resid, L.waves, mis);
+                           (const double*)y, (double*)resid, L.waves, mis, keep);
     switch (L.unroll) {
         case 1: LSEFIT_RES(1) break;
         case 2: LSEFIT_RES(2) break;

@@ -23,7 +23,7 @@ struct Launchers {
                               const double* grad_coef, int32_t coef_stride, void* gx, void* gy, const Launch& L,
                               int mis, hipStream_t st);
     static hipError_t residual(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y, void* resid,
-                               const Launch& L, int mis, hipStream_t st);
+                               const Launch& L, int mis, bool keep, hipStream_t st);
 
    private:
     template <int PREC, typename In>
