@@ -176,6 +176,26 @@ __device__ inline void minmax_segment(const In* __restrict__ x, int64_t lo, int6
     }
 }
 
+// x only, a short fit's points [lo, lo + n) by kGroup lanes (stream_group's pattern)
+template <typename In>
+__device__ inline void minmax_group(const In* __restrict__ x, int64_t lo, int n, MinMax<In>& r) {
+    constexpr int VW = VecOf<In>::W;
+    constexpr int U = 4;
+    using V = typename VecOf<In>::type;
+    const int gl = lane_id() % kGroup;
+    const int nv = n / VW, tail = n - nv * VW;
+    const In* px = x + lo;
+    if (gl < tail) r.add(px[nv * VW + gl]);
+    for (int j = gl; j < nv; j += kGroup * U) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            v[u] = *reinterpret_cast<const typename VecAny<In>::type*>(px + min(j + u * kGroup, nv - 1) * VW);
+#pragma unroll
+        for (int u = 0; u < U; ++u) r.template vec<V, VW>(v[u]);   // a vector read twice changes no extreme
+    }
+}
+
 // The block pairs (min, max) of a single fit's range pass, past the K sums per
 // block that the power-sum pass is about to write (the workspace holds both:
 // layout in api.hip), so that every block of that pass can fold them itself
@@ -245,9 +265,17 @@ __global__ void __launch_bounds__(256)
     k_range_cheb_batch(FitDesc d, Work w, const In* __restrict__ x, int64_t W, int mis, int maxm) {
     const KernelClock kclock_(w.clock);
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
-    walk_segments_ahead(d, w.tile_start, w.pstatus, w.rec, rec_len(maxm), wave, W,
-                        [&](int64_t, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
-        if (mt.st != LSEFIT_OK) return;
+    auto short_fits = [&](int64_t f, bool mine, const SegMeta& mt) {
+        MinMax<In> r;
+        minmax_group(x, mt.lo, mine ? (int)(mt.hi - mt.lo) : 0, r);
+        const double a = group8_extreme<false>((double)r.lo), b = group8_extreme<true>((double)r.hi);
+        if (mine && lane_id() % kGroup == 0) {
+            w.part[2 * (wave + f)] = a;
+            w.part[2 * (wave + f) + 1] = b;
+        }
+    };
+    walk_grouped(d, w.tile_start, w.pstatus, w.rec, rec_len(maxm), wave, W, (int)sizeof(In), short_fits,
+                 [&](int64_t, int64_t lo, int64_t hi, int64_t slot, const SegMeta&) {
         MinMax<In> r;
         minmax_segment(x, lo, hi, mis, r);
         const double a = wave_min((double)r.lo), b = wave_max((double)r.hi);
@@ -294,17 +322,22 @@ __device__ inline void cheb_block_partial(const Work& w, const double (&v)[K]) {
     }
 }
 
-// the wave's [C_1..C_M, E_1..E_M, D_0..D_M] (the V = 2T sums times 1/2 or 1/4: exact)
-template <int M>
-__device__ inline void cheb_wave_sums(const AccCheb<M>& acc, double (&v)[nacc(M)]) {
+// [C_1..C_M, E_1..E_M, D_0..D_M] over the lanes that `sum` adds (the V = 2T sums
+// times 1/2 or 1/4: exact)
+template <int M, class Sum>
+__device__ inline void cheb_scaled_sums(const AccCheb<M>& acc, double (&v)[nacc(M)], Sum&& sum) {
 #pragma unroll
     for (int k = 0; k < M; ++k) {
-        v[k] = 0.5 * wave_sum(acc.C[k]);
-        v[M + k] = 0.25 * wave_sum(acc.E[k]);
+        v[k] = 0.5 * sum(acc.C[k]);
+        v[M + k] = 0.25 * sum(acc.E[k]);
     }
-    v[2 * M] = wave_sum(acc.D[0]);
+    v[2 * M] = sum(acc.D[0]);
 #pragma unroll
-    for (int j = 1; j <= M; ++j) v[2 * M + j] = 0.5 * wave_sum(acc.D[j]);
+    for (int j = 1; j <= M; ++j) v[2 * M + j] = 0.5 * sum(acc.D[j]);
+}
+template <int M>
+__device__ inline void cheb_wave_sums(const AccCheb<M>& acc, double (&v)[nacc(M)]) {
+    cheb_scaled_sums(acc, v, [](double a) { return wave_sum(a); });
 }
 
 // the single-fit sweep of stream_strided (same points, same order per lane)
@@ -408,8 +441,7 @@ __global__ void __launch_bounds__(256)
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
     const int stride = nacc(maxm);
     const int rl = rec_len(maxm);
-    walk_segments_ahead(d, w.tile_start, w.pstatus, w.rec, rl, wave, W,
-                        [&](int64_t, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
+    auto one_fit = [&](int64_t, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
         if (mt.st != LSEFIT_OK) return;
         const double c = mt.c;
         const double inv_s = 1.0 / mt.s;
@@ -425,7 +457,39 @@ __global__ void __launch_bounds__(256)
                 for (int k = 0; k < nacc(M); ++k) out[k] = v[k];
         };
         dispatch_degree<MAXC>(mt.deg, body);
-    });
+    };
+    if constexpr (MAXC <= 4) {
+        // short fits, kGroups at a time and those of one degree together (the sums
+        // of a higher degree do not hold a lower one's): 65,536 fits of 16 to 256
+        // float32 points 116 -> 37 us.  Above degree 4 the sums of a fit are too many
+        // for 8 lanes to carry at this rate (degrees to 8, 64 to 1,000 points: 57 us
+        // one fit at a time, 77 grouped; 4,096 points at degree 12, which only pay
+        // the larger kernel's registers: 42 and 65 us).
+        auto short_fits = [&](int64_t f, bool mine, const SegMeta& mt) {
+            uint64_t left = __ballot(mine);
+            while (left) {
+                const int deg = __builtin_amdgcn_readlane(mt.deg, __ffsll((unsigned long long)left) - 1);
+                const bool now = mine && mt.deg == deg;
+                left &= ~__ballot(now);
+                auto body = [&]<int M>() {
+                    AccCheb<M> acc;
+                    acc.init(mt.c, 1.0 / mt.s);
+                    stream_group<kGroupUnroll>(x, y, mt.lo, now ? (int)(mt.hi - mt.lo) : 0, acc);
+                    double v[nacc(M)];
+                    cheb_scaled_sums(acc, v, [](double a) { return group8_sum(a); });
+                    double* __restrict__ out = w.part + (wave + f) * stride;
+                    if (now && lane_id() % kGroup == 0) {
+#pragma unroll
+                        for (int k = 0; k < nacc(M); ++k) out[k] = v[k];
+                    }
+                };
+                dispatch_degree<MAXC>(deg, body);
+            }
+        };
+        walk_grouped(d, w.tile_start, w.pstatus, w.rec, rl, wave, W, (int)sizeof(In), short_fits, one_fit);
+    } else {
+        walk_segments_ahead(d, w.tile_start, w.pstatus, w.rec, rl, wave, W, one_fit);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -619,7 +683,16 @@ __global__ void __launch_bounds__(256) k_finish_cheb_batch(FitDesc d, Work w, in
     }
 }
 
-// Batch of degrees <= 4, one fit per thread: the thread sums its fit's partial
+// A batch's finish: one fit per thread up to degree 4 always, and up to degree 8
+// where the batch has enough fits; else one wave per fit, whose time grows with
+// the batch from 2,048 fits on.  Measured, wave / thread per fit, degree 5: 9 / 13 us
+// at 2,000 fits, 18 / 13 at 4,000, 162 / 13 at 40,000; degree 6: 20 / 20 at 4,000;
+// degree 8: 45 / 44 at 8,000, 85 / 36 at 16,000, 210 / 31 at 40,000.
+inline bool cheb_lane_finish(int maxm, int64_t batch) {
+    return maxm <= 4 || (maxm <= 6 && batch >= 4096) || (maxm <= 8 && batch >= 8192);
+}
+
+// Batch of degrees <= MAXC (4 or 8), one fit per thread: the thread sums its fit's partial
 // slots in wave order, forms C_0..C_2M (C_(M+j) = 2 E_j - C_(M-j)) and the Gram
 // system G_jk = (C_(j+k) + C_|j-k|)/2, G c = D, in its registers and solves it
 // (matrix_gepp / matrix_cholesky: the pivot and singular rules of the wave
@@ -1113,8 +1186,10 @@ hipError_t launch_finish_cheb(const FitDesc& d, const Work& w, int maxm, int64_t
         dispatch_degree<kChebMax>(d.degree, body);
         return hipGetLastError();
     }
-    if (maxm <= 4 && !fz.write_b && !fz.moments_out) {
-        launch_timed(k_finish_cheb_lane<4>, dim3((d.batch + 255) / 256), dim3(256), st, d, w, W, maxm, fz);
+    if (cheb_lane_finish(maxm, d.batch) && !fz.write_b && !fz.moments_out) {
+        const dim3 grid((d.batch + 255) / 256), block(256);
+        if (maxm <= 4) launch_timed(k_finish_cheb_lane<4>, grid, block, st, d, w, W, maxm, fz);
+        else launch_timed(k_finish_cheb_lane<8>, grid, block, st, d, w, W, maxm, fz);
         return hipGetLastError();
     }
     int64_t blocks = (d.batch + 3) / 4;

@@ -122,6 +122,14 @@ __device__ inline double wave_extreme(double v) {
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
     return __hiloint2double(hi, lo);
 }
+// over each group of 8 consecutive lanes
+template <bool MAX>
+__device__ inline double group8_extreme(double v) {
+    auto op = [](double a, double b) { return MAX ? fmax(a, b) : fmin(a, b); };
+    v = op(v, dpp_f64_keep<0xb1, 0xf>(v));
+    v = op(v, dpp_f64_keep<0x4e, 0xf>(v));
+    return op(v, dpp_f64_keep<0x141, 0xf>(v));
+}
 __device__ inline double wave_min(double v) { return wave_extreme<false>(v); }
 __device__ inline double wave_max(double v) { return wave_extreme<true>(v); }
 

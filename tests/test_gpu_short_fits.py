@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from gpu_common import announce, normwise, to_dev, torch
-from oracle import adjoint, fp64
+from oracle import adjoint, cheb, fp64
 from paper_1512_08017_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -125,3 +125,64 @@ def test_short_fits_backward(dtype, maxdeg, count, shift, solver):
             np.abs(ref["dy"] * poly.polyval(t, poly.polyder(ref["b"]))))
         assert np.max(np.abs(gx[lo:hi] - ref["dx"])) <= tol * size, (f, hi - lo, m)
         assert np.max(np.abs(gy[lo:hi] - ref["dy"])) <= tol * np.max(np.abs(ref["dy"])), (f, hi - lo, m)
+
+
+def cheb_check(bf, coef, status, maxdeg, fits):
+    for f in fits:
+        m, lo, hi = int(bf.degrees[f]), bf.offsets[f], bf.offsets[f + 1]
+        if hi - lo < m + 1:
+            assert status[f] == 2 and np.isnan(coef[f, : m + 1]).all()
+            continue
+        V = np.polynomial.chebyshev.chebvander(bf.x[lo:hi].astype(np.float64), m)
+        tol = max(1e-12, 1e3 * EPS * np.linalg.cond(V.T @ V))
+        if tol > 1e-3:
+            continue
+        ref = cheb.fit_cheb(bf.x[lo:hi], bf.y[lo:hi], m, 0.0, 1.0)
+        assert status[f] == 0, (f, hi - lo, m, status[f])
+        assert normwise(coef[f, : m + 1], np.asarray(ref["c"], float)) <= tol, (f, hi - lo, m)
+
+
+@pytest.mark.parametrize("dtype,maxdeg,count,shift,given", [(np.float32, 3, 8, 0, True), (np.float64, 4, 7, 1, True),
+                                                            (np.float32, 4, 1, 2, True), (np.float32, 6, 9, 0, True),
+                                                            (np.float32, 3, 9, 1, False)])
+def test_short_fits_chebyshev(dtype, maxdeg, count, shift, given):
+    """The same batches in the Chebyshev basis (grouped up to degree 4, the range pass at
+    every degree; mixed degrees in a group)."""
+    announce(f"short fits Chebyshev {np.dtype(dtype).name} degree <= {maxdeg} count {count} shift {shift} given {given}")
+    n = lengths(count, 80 + maxdeg)
+    deg = np.random.default_rng(count + 5).integers(1, maxdeg + 1, n.size).astype(np.int32)
+    bf = W.random_batch(n, deg, seed=81 + maxdeg, dtype=dtype)
+    pad = np.zeros(2, dtype)
+    x = to_dev(np.concatenate([pad[:shift], bf.x]))[shift:]
+    y = to_dev(np.concatenate([pad[:1 if shift else 0], bf.y]))[1 if shift else 0:]
+    kw = dict(center=0.0, scale=1.0) if given else {}
+    coef, status, _ = lf.fit_batched(x, y, to_dev(bf.offsets), to_dev(bf.degrees), maxdeg, basis="chebyshev",
+                                     coef_stride=maxdeg + 3, **kw)
+    torch.cuda.synchronize()
+    coef, status = coef.cpu().numpy(), status.cpu().numpy()
+    if given:
+        cheb_check(bf, coef, status, maxdeg, range(bf.batch))
+        return
+    for f in range(bf.batch):   # the exact extent of each fit
+        m, lo, hi = int(deg[f]), bf.offsets[f], bf.offsets[f + 1]
+        if hi - lo < m + 1 or status[f] != 0:
+            continue
+        a, b = float(bf.x[lo:hi].min()), float(bf.x[lo:hi].max())
+        assert tuple(coef[f, m + 1: m + 3]) == (0.5 * b + 0.5 * a, 0.5 * b - 0.5 * a), f
+    assert (status[n >= 64] == 0).all()
+
+
+@pytest.mark.parametrize("batch,maxdeg", [(4095, 6), (4096, 5), (4097, 6), (8191, 8), (8192, 8), (8193, 7)])
+def test_chebyshev_finish_forms(batch, maxdeg):
+    """The batch sizes where the finish turns from a wave per fit to a thread per fit."""
+    announce(f"Chebyshev finish of {batch} fits of degree <= {maxdeg}")
+    rng = np.random.default_rng(batch)
+    deg = rng.integers(1, maxdeg + 1, batch).astype(np.int32)
+    bf = W.random_batch(rng.integers(40, 120, batch), deg, seed=batch)
+    for solver in ("gepp", "cholesky"):
+        coef, status, _ = lf.fit_batched(to_dev(bf.x), to_dev(bf.y), to_dev(bf.offsets), to_dev(bf.degrees), maxdeg,
+                                         basis="chebyshev", center=0.0, scale=1.0, coef_stride=maxdeg + 1, solver=solver)
+        torch.cuda.synchronize()
+        coef, status = coef.cpu().numpy(), status.cpu().numpy()
+        assert (status == 0).all()
+        cheb_check(bf, coef, status, maxdeg, list(range(0, batch, 97)) + [batch - 2, batch - 1])
