@@ -58,6 +58,19 @@ struct GivensQR {
     // offset of Rb_(i, i+1) in r
     static constexpr int row_at(int i) { return i * N - i * (i + 1) / 2; }
 
+    // one entry of a rotation.  v' = v - x r, r' = c r + s v = r + s v': the last
+    // form is one operation shorter, and exact enough while c is not small.  Where a
+    // row of real size meets one that holds only the rounding of equal t (c near 0,
+    // r up to 1/eps), r + s v' cancels r's digits with everything that came in: the
+    // guarded form, which such rows go through, takes c r + s v
+    template <bool GUARD>
+    static __device__ inline void rotate(double xi, double cb, double sb, double& v, double& r) {
+        const double old = v;
+        v = fma(-xi, r, v);
+        if constexpr (GUARD) r = fma(cb, r, sb * old);
+        else r = fma(sb, v, r);
+    }
+
     // include the row (x; y) of weight w whose entries before column S are zero.
     // GUARD = false when every d_i (i >= S) is already positive: then
     // d_i' >= d_i > 0 (w x_i^2 >= 0), the zero-weight case cannot occur, and
@@ -79,21 +92,24 @@ struct GivensQR {
 #pragma unroll
             for (int k = i + 1; k < N; ++k) {
                 double& rik = r[row_at(i) + k - i - 1];
-                x[k] = fma(-xi, rik, x[k]);
-                rik = fma(sb, x[k], rik);
+                rotate<GUARD>(xi, cb, sb, x[k], rik);
             }
-            y = fma(-xi, th[i], y);
-            th[i] = fma(sb, y, th[i]);
+            rotate<GUARD>(xi, cb, sb, y, th[i]);
         }
         e = fma(w * y, y, e);
     }
 
-    // every d_i of columns 1.. positive (d_0 counts the rows, so it is too
-    // once one row is in): from then on data rows need no zero-weight guard
-    __device__ inline bool settled() const {
+    // every d_i of columns 1.. above what rounding leaves there when all t are equal
+    // (some (8 eps)^2 = 2^-98 of d_0 t^2i, t2 the largest t^2 so far): from then on
+    // data rows need neither the zero-weight guard nor the guarded rotation
+    __device__ inline bool settled(double t2) const {
         bool ok = true;
+        double floor = d[0] * 0x1p-80;
 #pragma unroll
-        for (int i = 1; i < N; ++i) ok = ok && d[i] > 0.0;
+        for (int i = 1; i < N; ++i) {
+            floor *= t2;
+            ok = ok && d[i] > floor;
+        }
         return ok;
     }
 
@@ -178,6 +194,8 @@ struct AccQR {
     static constexpr int N = M + 1;
     GivensQR<N> q;
     double inv_s, nc;
+    double t2 = 0.0;        // largest t^2 of the lane until its factor has settled
+    bool settled = false;   // (d_i only grow, so once it has, it stays so)
     const double* tab;   // kRecipRows reciprocals 1/(j+1) in LDS (fill_recip_rows)
     __device__ inline void init(double c, double is, const double* t) {
         q.zero();
@@ -200,16 +218,22 @@ struct AccQR {
         for (int e = 0; e < VW; ++e) point<GUARD, TABLE>((double)xv[e], (double)yv[e]);
     }
     // a lane whose factor has settled (after its first N rows or so, unless
-    // its t stay at 0) takes the rows without the zero-weight selects, and
+    // its t stay equal) takes the rows without the zero-weight selects, and
     // while its row count stays inside the table, the first column's
     // reciprocals from it
     template <typename V, int VW>
     __device__ inline void vec(const V& xv, const V& yv) {
-        if (q.settled()) {
+        if (settled) {
             if (q.d[0] <= (double)(kRecipRows - VW)) rows<false, true, V, VW>(xv, yv);
             else rows<false, false, V, VW>(xv, yv);
         } else {
             rows<true, false, V, VW>(xv, yv);
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                const double t = fma((double)xv[e], inv_s, nc);
+                t2 = fmax(t2, t * t);
+            }
+            settled = q.settled(t2);
         }
     }
     __device__ inline void scalar(double xv, double yv) { point(xv, yv); }
