@@ -243,12 +243,12 @@ struct AccQR {
 // l + off, row by row; the senders (lanes >= off) do not change during the
 // level, and every lane takes part in the shuffles.  Fixed order, so the
 // result is reproducible.
-template <int N>
+template <int N, int LANES = kWave>
 __device__ inline void wave_merge(GivensQR<N>& q) {
     using Q = GivensQR<N>;
-    const int lane = lane_id();
+    const int lane = lane_id() % LANES;   // LANES < 64: within each group of that many lanes
 #pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) {
+    for (int off = LANES / 2; off >= 1; off >>= 1) {
         const bool recv = lane < off;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -291,9 +291,7 @@ __device__ inline void block_merge_store(const Work& w, GivensQR<N>& q) {
 // worth registers: one vector per round and a register budget (96 VGPRs,
 // 5 waves per SIMD, up to m = 3; 128 and 4 at m = 4; 256 above) keep the
 // compiler from hoisting across points, and the extra waves cover the
-// dependence chain through each column's reciprocal.  (The batched kernel
-// takes the budget of its largest degree, 4 or 8: at 5 waves per SIMD its
-// degree-3 form was slower.)
+// dependence chain through each column's reciprocal.
 constexpr int qr_waves_per_eu(int M) { return M <= 3 ? 5 : (M <= 4 ? 4 : 2); }
 
 template <typename In, int U, int M>
@@ -777,10 +775,22 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
 // ---------------------------------------------------------------------------
 // batches: each wave factors its segment of every fit it streams, merges the
 // factor to lane 0 and writes it to the fit's slot w + f (qr_len(maxm)
-// doubles); one thread per fit then merges the fit's slots in wave order
+// doubles); one thread per fit then merges the fit's slots in wave order.
+//
+// Bound by the rotations' float64 chain, and for short fits by the merge: 6
+// levels of dependent rotations are what a whole fit of 64 points costs.  So up
+// to degree 4 short fits go 8 to a wave, as in the moment pass (3 levels, and 8
+// fits share them).  65,536 fits, float32, this pass: 16 points at degree 2
+// 184 -> 31 us; 64 points at degree 3 239 -> 66 us; 16 to 256 points at degree 3
+// 257 -> 114 us; 16 to 1,024 and more points unchanged within 2% (4,096 points 71
+// us before and after; 16 to 65,536 points 1.6 ms).  Above degree 4 the factor
+// alone takes the register file (and 208 to 496 bytes of scratch), so there the
+// walk stays one fit at a time, its descriptors read ahead.
+// 3 waves per SIMD up to degree 4 (4 before): at 4 both loops together left
+// fits of 4,096 points 2 to 7% slower, at 3 they are no slower than before.
 // ---------------------------------------------------------------------------
 template <typename In, int MAXC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_waves_per_eu(MAXC))))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXC <= 4 ? 3 : 2)))
     k_qr_batch(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W,
                int mis, int maxm) {
     const KernelClock kclock_(w.clock);
@@ -789,10 +799,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_wav
     const int rl = rec_len(maxm);
     __shared__ double tab[kRecipRows];
     fill_recip_rows(tab);
-    walk_segments(d, w.tile_start, wave, W, [&](int64_t f, int64_t lo, int64_t hi, int64_t slot) {
-        if (w.pstatus[f] != LSEFIT_OK) return;
-        const double c = w.rec[f * rl + 0];
-        const double inv_s = 1.0 / w.rec[f * rl + 1];
+    auto one_fit = [&](int64_t, int64_t lo, int64_t hi, int64_t slot, const SegMeta& mt) {
+        if (mt.st != LSEFIT_OK) return;
+        const double c = mt.c, inv_s = 1.0 / mt.s;
         double* __restrict__ out = w.part + slot * stride;
         auto body = [&]<int M>() {
             AccQR<M> acc;
@@ -804,8 +813,35 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_wav
                 for (int j = 0; j < GivensQR<M + 1>::LEN; ++j) out[j] = acc.q.flat(j);
             }
         };
-        dispatch_degree<MAXC>(fit_deg(d, f), body);
-    });
+        dispatch_degree<MAXC>(mt.deg, body);
+    };
+    if constexpr (MAXC <= 4) {
+        // short fits, kGroups at a time and those of one degree together: 8 lanes
+        // factor a fit's rows and merge in 3 levels instead of 6
+        auto short_fits = [&](int64_t f, bool mine, const SegMeta& mt) {
+            uint64_t left = __ballot(mine);
+            while (left) {
+                const int deg = __builtin_amdgcn_readlane(mt.deg, __ffsll((unsigned long long)left) - 1);
+                const bool now = mine && mt.deg == deg;
+                left &= ~__ballot(now);
+                auto body = [&]<int M>() {
+                    AccQR<M> acc;
+                    acc.init(mt.c, 1.0 / mt.s, tab);
+                    stream_group<1>(x, y, mt.lo, now ? (int)(mt.hi - mt.lo) : 0, acc);
+                    wave_merge<M + 1, kGroup>(acc.q);
+                    double* __restrict__ out = w.part + (wave + f) * stride;
+                    if (now && lane_id() % kGroup == 0) {
+#pragma unroll
+                        for (int j = 0; j < GivensQR<M + 1>::LEN; ++j) out[j] = acc.q.flat(j);
+                    }
+                };
+                dispatch_degree<MAXC>(deg, body);
+            }
+        };
+        walk_grouped(d, w.tile_start, w.pstatus, w.rec, rl, wave, W, (int)sizeof(In), short_fits, one_fit);
+    } else {
+        walk_segments_ahead(d, w.tile_start, w.pstatus, w.rec, rl, wave, W, one_fit);
+    }
 }
 
 template <int MAXC>

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from gpu_common import announce, normwise, to_dev, torch
-from oracle import adjoint, cheb, fp64
+from oracle import adjoint, cheb, fp64, qr
 from paper_1512_08017_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -186,3 +186,35 @@ def test_chebyshev_finish_forms(batch, maxdeg):
         coef, status = coef.cpu().numpy(), status.cpu().numpy()
         assert (status == 0).all()
         cheb_check(bf, coef, status, maxdeg, list(range(0, batch, 97)) + [batch - 2, batch - 1])
+
+
+@pytest.mark.parametrize("dtype,maxdeg,count,shift", [(np.float32, 1, 8, 0), (np.float64, 3, 7, 1), (np.float32, 4, 1, 2),
+                                                      (np.float64, 2, 9, 0), (np.float32, 6, 9, 1)])
+def test_short_fits_qr(dtype, maxdeg, count, shift):
+    """The same batches by rotations (grouped up to degree 4).  Both sides are QR factorisations of
+    the same rows: their coefficients differ by roundings times cond(V), and by its square where the
+    residual is of the size of the values."""
+    announce(f"short fits QR {np.dtype(dtype).name} degree <= {maxdeg} count {count} shift {shift}")
+    n = lengths(count, 90 + maxdeg)
+    deg = np.random.default_rng(count + 9).integers(1, maxdeg + 1, n.size).astype(np.int32)
+    bf = W.random_batch(n, deg, seed=91 + maxdeg, dtype=dtype)
+    pad = np.zeros(2, dtype)
+    x = to_dev(np.concatenate([pad[:shift], bf.x]))[shift:]
+    y = to_dev(np.concatenate([pad[:1 if shift else 0], bf.y]))[1 if shift else 0:]
+    coef, status, sse, _ = lf.fit_qr_batched(x, y, to_dev(bf.offsets), to_dev(bf.degrees), maxdeg, center=0.0, scale=1.0)
+    torch.cuda.synchronize()
+    coef, status, sse = coef.cpu().numpy(), status.cpu().numpy(), sse.cpu().numpy()
+    for f in range(bf.batch):
+        m, lo, hi = int(deg[f]), bf.offsets[f], bf.offsets[f + 1]
+        if hi - lo < m + 1:
+            assert status[f] == 2, (f, hi - lo, status[f])
+            continue
+        tol = gate(bf.x[lo:hi], m, 0.0, 1.0)     # holds cond(V)^2
+        if tol > 1e-3:
+            continue
+        assert status[f] == 0, (f, hi - lo, m, status[f])
+        b_ref = qr.lstsq_qr(bf.x[lo:hi], bf.y[lo:hi], m, 0.0, 1.0)
+        assert normwise(coef[f, : m + 1], b_ref) <= tol, (f, hi - lo, m)
+        r = bf.y[lo:hi].astype(np.float64) - np.polynomial.polynomial.polyval(bf.x[lo:hi].astype(np.float64), b_ref)
+        yy = float(np.sum(bf.y[lo:hi].astype(np.float64) ** 2))
+        assert abs(sse[f] - float(r @ r)) <= tol * yy, (f, hi - lo, m)
