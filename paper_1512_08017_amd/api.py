@@ -49,7 +49,8 @@ def _native():
         L = _lib.load()
         from . import _bind as module   # built next to the library; no other form of it
         module.init(*(ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in (
-            "lsefit_workspace_bytes", "fit_single", "fit_qr", "fit_residuals", "fit_batched", "fit_backward")))
+            "lsefit_workspace_bytes", "fit_single", "fit_qr", "fit_residuals", "fit_batched", "fit_backward",
+            "fit_qr_batched")))
         _bind = module
     return _bind
 
@@ -260,6 +261,13 @@ def fit_qr_batched(x, y, offsets, degrees, max_degree: int, center=None, scale=N
                    out=None):
     """Independent fits over CSR segments through the streaming QR route;
     returns (coef [B, stride], status [B], sse [B], ws)."""
+    oc, os_, oe = (None, None, None) if out is None else out
+    r = _native().fit_qr_batched(x, y, offsets, degrees, max_degree, center, scale, coef_stride, ws, oc, os_, oe,
+                                 "f64", 0, "gepp", "monomial")
+    if r is not None:
+        if type(r) is int:
+            check(r, "fit_qr_batched")
+        return r
     _check_batch(x, y, offsets, degrees)
     L = _lib.load()
     B = degrees.numel()

@@ -1,6 +1,6 @@
 // Argument marshalling of the Python surface in native code: the checks, the
-// result tensors and the C-ABI call of fit, fit_qr, residuals, fit_batched and
-// fit_backward in one step each.  A small fit is a few microseconds of GPU
+// result tensors and the C-ABI call of fit, fit_qr, residuals, fit_batched,
+// fit_qr_batched and fit_backward in one step each.  A small fit is a few microseconds of GPU
 // work; on the MI355X machine's host a call took 18.3 us with the same steps
 // through ctypes and Python-level tensor calls, and takes 12.6 us with them here
 // (two kernel launches included); the forward and backward of a batch through
@@ -32,15 +32,16 @@ struct Api {
     decltype(&::fit_residuals) residuals = nullptr;
     decltype(&::fit_batched) batched = nullptr;
     decltype(&::fit_backward) backward = nullptr;
+    decltype(&::fit_qr_batched) qr_batched = nullptr;
 } api;
 
 PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (n != 6) {
-        PyErr_SetString(PyExc_TypeError, "init takes six addresses");
+    if (n != 7) {
+        PyErr_SetString(PyExc_TypeError, "init takes seven addresses");
         return nullptr;
     }
-    void* p[6];
-    for (int i = 0; i < 6; ++i) {
+    void* p[7];
+    for (int i = 0; i < 7; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
         if (!p[i]) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null address");
@@ -53,6 +54,7 @@ PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
     api.residuals = (decltype(api.residuals))p[3];
     api.batched = (decltype(api.batched))p[4];
     api.backward = (decltype(api.backward))p[5];
+    api.qr_batched = (decltype(api.qr_batched))p[6];
     Py_RETURN_NONE;
 }
 
@@ -264,7 +266,7 @@ PyObject* fit_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
     at::Tensor ws, coef, status;
     if (!plan && !workspace(a[11], api.workspace_bytes(B > 1 ? B : 1, o.degree, nullptr), p, &ws)) Py_RETURN_NONE;
-    if (a[12] != Py_None) {
+    if (a[12] != Py_None || a[13] != Py_None) {
         const at::Tensor *c, *s;
         if (!tensor(a[12], &c) || !tensor(a[13], &s)) Py_RETURN_NONE;
         coef = *c;
@@ -314,11 +316,50 @@ PyObject* fit_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
+// fit_qr_batched(x, y, offsets, degrees, max_degree, center, scale, coef_stride, ws, coef, status, sse,
+//                precision, refine, solver, basis) -> (coef, status, sse, ws); the last four as the options have them
+PyObject* fit_qr_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    Points p;
+    lsefit_options o;
+    const at::Tensor *off, *deg;
+    if (n != 16 || !points(a[0], a[1], &p) || !batch(a[2], a[3], p, &off, &deg) ||
+        !options(a[4], a[12], a[13], a[5], a[6], a[14], a[15], &o))
+        Py_RETURN_NONE;
+    const int64_t B = deg->numel();
+    int64_t stride = 0;
+    if (a[7] != Py_None && !integer(a[7], &stride)) Py_RETURN_NONE;
+    if (stride == 0) stride = o.degree + 1;
+    if (stride < 1) Py_RETURN_NONE;
+    at::Tensor ws, coef, status, sse;
+    if (!workspace(a[8], api.workspace_bytes(B > 1 ? B : 1, o.degree, nullptr), p, &ws)) Py_RETURN_NONE;
+    if (a[9] != Py_None || a[10] != Py_None || a[11] != Py_None) {
+        const at::Tensor *c, *s, *e;
+        if (!tensor(a[9], &c) || !tensor(a[10], &s) || !tensor(a[11], &e)) Py_RETURN_NONE;
+        coef = *c;
+        status = *s;
+        sse = *e;
+    } else {
+        coef = at::zeros({B, stride}, p.x->options().dtype(at::kDouble).requires_grad(false));
+        status = ints(p, B);
+        sse = doubles(p, B);
+    }
+    const int code = call([&] {
+        return api.qr_batched(p.x->data_ptr(), p.y->data_ptr(), at_ptr<int64_t>(*off), at_ptr<int32_t>(*deg), B, p.dt,
+                              &o, ws.data_ptr(), (size_t)ws.numel(), at_ptr<double>(coef), (int32_t)stride,
+                              at_ptr<int32_t>(status), at_ptr<double>(sse), p.stream);
+    });
+    if (code) return PyLong_FromLong(code);
+    return wrap({coef, status, sse, ws});
+    END_HANDLE_TH_ERRORS
+}
+
 PyMethodDef methods[] = {{"init", (PyCFunction)(void*)init, METH_FASTCALL, nullptr},
                          {"fit", (PyCFunction)(void*)fit, METH_FASTCALL, nullptr},
                          {"fit_qr", (PyCFunction)(void*)fit_qr, METH_FASTCALL, nullptr},
                          {"residuals", (PyCFunction)(void*)residuals, METH_FASTCALL, nullptr},
                          {"fit_batched", (PyCFunction)(void*)fit_batched, METH_FASTCALL, nullptr},
+                         {"fit_qr_batched", (PyCFunction)(void*)fit_qr_batched, METH_FASTCALL, nullptr},
                          {"fit_backward", (PyCFunction)(void*)fit_backward, METH_FASTCALL, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bind", "argument marshalling in native code", -1, methods};

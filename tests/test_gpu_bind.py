@@ -103,3 +103,29 @@ def test_what_is_refused_stays_refused(monkeypatch):
     assert torch.equal(lf.fit(torch.nn.Parameter(x, requires_grad=False), y, 2).coef, want)
     assert torch.equal(lf.fit(x, y, np.int32(2)).coef, want)
     assert lf.fit_batched(x[:0], y[:0], off[:1] * 0, dg[:0], 2)[0].shape == (0, 3)
+
+
+@pytest.mark.parametrize("kw", [{}, {"coef_stride": 7}, {"center": 0.25, "scale": 2}])
+def test_qr_batched(monkeypatch, kw):
+    bf = W.random_batch([50, 0, 2, 700, 3000, 90], [1, 2, 3, 2, 3, 1], seed=4)
+    x, y, off, dg = (to_dev(v) for v in (bf.x, bf.y, bf.offsets, bf.degrees))
+    a, b = both(monkeypatch, lambda: lf.fit_qr_batched(x, y, off, dg, 3, **kw))
+    assert all(same(u, v) for u, v in zip(a[:3], b[:3])) and a[3].numel() == b[3].numel()
+    out = tuple(torch.full_like(v, 3) for v in a[:3])
+    c = lf.fit_qr_batched(x, y, off, dg, 3, ws=a[3], out=out, **kw)
+    torch.cuda.synchronize()
+    assert all(u.data_ptr() == v.data_ptr() for u, v in zip(c[:3], out)) and c[3].data_ptr() == a[3].data_ptr()
+    assert same(c[0][:, :2], a[0][:, :2]) and same(c[1], a[1]) and same(c[2], a[2])
+    calls = [lambda: lf.fit_qr_batched(x, y, off.int(), dg, 3), lambda: lf.fit_qr_batched(x, y, off, dg, 9),
+             lambda: lf.fit_qr_batched(x, y, off, dg, 3, coef_stride=2), lambda: lf.fit_qr_batched(x[::2], y, off, dg, 3),
+             lambda: lf.fit_qr_batched(x, y, off, dg, 3, center=0.0, scale=0.0)]
+    for k, call in enumerate(calls):
+        seen = []
+        for native in (True, False):
+            with monkeypatch.context() as m:
+                if not native:
+                    m.setattr(api, "_bind", Declines())
+                with pytest.raises((TypeError, ValueError, RuntimeError, _lib.LsefitError)) as e:
+                    call()
+                seen.append((type(e.value), str(e.value)))
+        assert seen[0] == seen[1], (k, seen)
