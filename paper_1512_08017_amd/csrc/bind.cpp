@@ -62,7 +62,8 @@ PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
 bool tensor(PyObject* o, const at::Tensor** t) {
     if (!THPVariable_CheckExact(o)) return false;   // subclasses go the Python way
     *t = &THPVariable_Unpack(o);
-    return (*t)->defined() && (*t)->layout() == at::kStrided;
+    // functorch's wrappers (vmap, grad, jvp) have the exact type too, but no memory of their own
+    return (*t)->defined() && (*t)->layout() == at::kStrided && (*t)->has_storage();
 }
 bool integer(PyObject* o, int64_t* v) {
     if (!PyLong_Check(o)) return false;
@@ -107,6 +108,7 @@ bool options(PyObject* degree, PyObject* precision, PyObject* refine, PyObject* 
 
 struct Points {
     const at::Tensor *x, *y;
+    const void *px, *py;
     int64_t n;
     int32_t dt;
     void* stream;
@@ -119,6 +121,8 @@ bool points(PyObject* ox, PyObject* oy, Points* p) {
     if (x.scalar_type() != at::kFloat && x.scalar_type() != at::kDouble) return false;
     if (x.dim() != 1 || y.dim() != 1 || x.numel() != y.numel() || !x.is_contiguous() || !y.is_contiguous()) return false;
     if (x.is_neg() || y.is_neg()) return false;
+    p->px = x.data_ptr();
+    p->py = y.data_ptr();
     p->n = x.numel();
     p->dt = x.scalar_type() == at::kFloat ? LSEFIT_F32 : LSEFIT_F64;
     p->stream = (void*)c10::hip::getCurrentHIPStream(x.device().index()).stream();
@@ -159,14 +163,25 @@ template <class T>
 T* at_ptr(const at::Tensor& t) {
     return (T*)t.data_ptr();
 }
+// a workspace's memory (none with a plan, which brings its own)
+struct Space {
+    void* p = nullptr;
+    size_t bytes = 0;
+    Space() = default;
+    explicit Space(const at::Tensor& t) : p(t.data_ptr()), bytes((size_t)t.numel()) {}
+};
 
+// The library call, with the interpreter released.  Tensors are asked for their
+// memory before it (data_ptr may throw, and may run code that needs the
+// interpreter); the lambdas hold plain pointers and sizes only.
+struct Released {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~Released() { PyEval_RestoreThread(state); }
+};
 template <class F>
 int call(F&& f) {
-    int code;
-    Py_BEGIN_ALLOW_THREADS
-    code = (int)f();
-    Py_END_ALLOW_THREADS
-    return code;
+    const Released released;
+    return (int)f();
 }
 
 PyObject* wrap(std::initializer_list<at::Tensor> ts, const lsefit_options* o = nullptr) {
@@ -190,10 +205,10 @@ PyObject* fit(PyObject*, PyObject* const* a, Py_ssize_t n) {
         Py_RETURN_NONE;
     const int64_t m1 = o.degree + 1;
     const at::Tensor coef = doubles(p, 2 * m1), status = ints(p, 1), mom = doubles(p, 3 * m1 + 1);
-    const int code = call([&] {
-        return api.single(p.x->data_ptr(), p.y->data_ptr(), p.n, p.dt, &o, ws.data_ptr(), (size_t)ws.numel(),
-                          at_ptr<double>(coef), at_ptr<int32_t>(status), at_ptr<double>(mom), p.stream);
-    });
+    const Space sp(ws);
+    double *pc = at_ptr<double>(coef), *pm = at_ptr<double>(mom);
+    int32_t* ps = at_ptr<int32_t>(status);
+    const int code = call([&] { return api.single(p.px, p.py, p.n, p.dt, &o, sp.p, sp.bytes, pc, ps, pm, p.stream); });
     if (code) return PyLong_FromLong(code);
     return wrap({coef.narrow(0, 0, m1), coef.narrow(0, m1, m1), status, mom, ws}, &o);
     END_HANDLE_TH_ERRORS
@@ -211,10 +226,10 @@ PyObject* fit_qr(PyObject*, PyObject* const* a, Py_ssize_t n) {
         Py_RETURN_NONE;
     const int64_t m1 = o.degree + 1;
     const at::Tensor coef = doubles(p, 2 * m1), status = ints(p, 1), info = doubles(p, 3);
-    const int code = call([&] {
-        return api.qr(p.x->data_ptr(), p.y->data_ptr(), p.n, p.dt, &o, ws.data_ptr(), (size_t)ws.numel(),
-                      at_ptr<double>(coef), at_ptr<int32_t>(status), at_ptr<double>(info), p.stream);
-    });
+    const Space sp(ws);
+    double *pc = at_ptr<double>(coef), *pi = at_ptr<double>(info);
+    int32_t* ps = at_ptr<int32_t>(status);
+    const int code = call([&] { return api.qr(p.px, p.py, p.n, p.dt, &o, sp.p, sp.bytes, pc, ps, pi, p.stream); });
     if (code) return PyLong_FromLong(code);
     return wrap({coef.narrow(0, 0, m1), coef.narrow(0, m1, m1), status, info, ws}, &o);
     END_HANDLE_TH_ERRORS
@@ -228,15 +243,17 @@ PyObject* residuals(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 5 || !points(a[0], a[1], &p) || !PyLong_Check(a[2]) || !tensor(a[3], &ws) || !PyBool_Check(a[4]))
         Py_RETURN_NONE;
     if (ws->scalar_type() != at::kByte || !ws->is_contiguous()) Py_RETURN_NONE;
-    const lsefit_options* o = (const lsefit_options*)PyLong_AsVoidPtr(a[2]);
-    if (!o) Py_RETURN_NONE;
+    const lsefit_options* given = (const lsefit_options*)PyLong_AsVoidPtr(a[2]);
+    if (!given) Py_RETURN_NONE;
+    const lsefit_options o = *given;   // its owner may drop it once the interpreter is released
     const at::Tensor sse = doubles(p, 1);
     const bool store = a[4] == Py_True;
     const at::Tensor res = store ? at::empty_like(p.x->detach()) : at::Tensor();
+    const Space sp(*ws);
+    double* pe = at_ptr<double>(sse);
+    void* pr = store ? res.data_ptr() : nullptr;
     const int code = call([&] {
-        return api.residuals(p.x->data_ptr(), p.y->data_ptr(), nullptr, nullptr, 1, p.n, p.dt, o, nullptr,
-                             ws->data_ptr(), (size_t)ws->numel(), at_ptr<double>(sse), store ? res.data_ptr() : nullptr,
-                             p.stream);
+        return api.residuals(p.px, p.py, nullptr, nullptr, 1, p.n, p.dt, &o, nullptr, sp.p, sp.bytes, pe, pr, p.stream);
     });
     if (code) return PyLong_FromLong(code);
     return wrap({sse, res});   // an undefined tensor is None
@@ -275,10 +292,13 @@ PyObject* fit_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
         coef = at::zeros({B, stride}, p.x->options().dtype(at::kDouble).requires_grad(false));
         status = ints(p, B);
     }
+    const Space sp = plan ? Space() : Space(ws);
+    const int64_t* po = at_ptr<int64_t>(*off);
+    const int32_t* pd = at_ptr<int32_t>(*deg);
+    double* pc = at_ptr<double>(coef);
+    int32_t* ps = at_ptr<int32_t>(status);
     const int code = call([&] {
-        return api.batched(p.x->data_ptr(), p.y->data_ptr(), at_ptr<int64_t>(*off), at_ptr<int32_t>(*deg), B, p.dt, &o,
-                           plan, plan ? nullptr : ws.data_ptr(), plan ? 0 : (size_t)ws.numel(), at_ptr<double>(coef),
-                           (int32_t)stride, at_ptr<int32_t>(status), p.stream);
+        return api.batched(p.px, p.py, po, pd, B, p.dt, &o, plan, sp.p, sp.bytes, pc, (int32_t)stride, ps, p.stream);
     });
     if (code) return PyLong_FromLong(code);
     return wrap({coef, status, ws});
@@ -306,10 +326,15 @@ PyObject* fit_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!plan && (!ws || ws->scalar_type() != at::kByte || !ws->is_contiguous())) Py_RETURN_NONE;
     const at::Tensor gc = g->scalar_type() == at::kDouble && g->is_contiguous() ? *g : g->to(at::kDouble).contiguous();
     const at::Tensor gx = at::empty_like(p.x->detach()), gy = at::empty_like(p.y->detach());
+    const Space sp = plan ? Space() : Space(*ws);
+    const int64_t* po = at_ptr<int64_t>(*off);
+    const int32_t* pd = at_ptr<int32_t>(*deg);
+    const int64_t B = deg->numel();
+    const double* pg = at_ptr<double>(gc);
+    const int32_t stride = (int32_t)gc.size(-1);
+    void *px = gx.data_ptr(), *py = gy.data_ptr();
     const int code = call([&] {
-        return api.backward(p.x->data_ptr(), p.y->data_ptr(), at_ptr<int64_t>(*off), at_ptr<int32_t>(*deg), deg->numel(),
-                            p.dt, &o, plan, plan ? nullptr : ws->data_ptr(), plan ? 0 : (size_t)ws->numel(),
-                            at_ptr<double>(gc), (int32_t)gc.size(-1), gx.data_ptr(), gy.data_ptr(), p.stream);
+        return api.backward(p.px, p.py, po, pd, B, p.dt, &o, plan, sp.p, sp.bytes, pg, stride, px, py, p.stream);
     });
     if (code) return PyLong_FromLong(code);
     return wrap({gx, gy});
@@ -344,10 +369,13 @@ PyObject* fit_qr_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
         status = ints(p, B);
         sse = doubles(p, B);
     }
+    const Space sp(ws);
+    const int64_t* po = at_ptr<int64_t>(*off);
+    const int32_t* pd = at_ptr<int32_t>(*deg);
+    double *pc = at_ptr<double>(coef), *pe = at_ptr<double>(sse);
+    int32_t* ps = at_ptr<int32_t>(status);
     const int code = call([&] {
-        return api.qr_batched(p.x->data_ptr(), p.y->data_ptr(), at_ptr<int64_t>(*off), at_ptr<int32_t>(*deg), B, p.dt,
-                              &o, ws.data_ptr(), (size_t)ws.numel(), at_ptr<double>(coef), (int32_t)stride,
-                              at_ptr<int32_t>(status), at_ptr<double>(sse), p.stream);
+        return api.qr_batched(p.px, p.py, po, pd, B, p.dt, &o, sp.p, sp.bytes, pc, (int32_t)stride, ps, pe, p.stream);
     });
     if (code) return PyLong_FromLong(code);
     return wrap({coef, status, sse, ws});
