@@ -55,6 +55,11 @@ def _native():
     return _bind
 
 
+def _plan_address(plan):
+    """What the native module takes for a plan: None without one; it declines 0, a closed one."""
+    return None if plan is None else plan.handle.value if plan.handle else 0
+
+
 def options(degree: int, precision: str = "f64", refine: int = 1, center=None, scale=None,
             solver: str = "gepp", basis: str = "monomial", output_basis: str = "x") -> Options:
     if precision not in _PREC:
@@ -427,8 +432,7 @@ def fit_batched(x, y, offsets, degrees, max_degree: int, precision: str = "f64",
     t-basis coefficients of t = (x - c)/s and the fit's c and s."""
     oc, os_ = (None, None) if out is None else out
     r = _native().fit_batched(x, y, offsets, degrees, max_degree, precision, refine, center, scale,
-                              None if plan is None else plan.handle.value, coef_stride, ws, oc, os_, solver, basis,
-                              output_basis)
+                              _plan_address(plan), coef_stride, ws, oc, os_, solver, basis, output_basis)
     if r is not None:
         if type(r) is int:
             check(r, "fit_batched")
@@ -460,7 +464,7 @@ def fit_backward(x, y, offsets, degrees, max_degree, grad_coef, ws=None, plan=No
     """dL/dx, dL/dy from dL/da (grad_coef [B, stride] float64) after fit_batched; for
     basis="chebyshev" (given center and scale) grad_coef is dL/dc of the Chebyshev coefficients."""
     r = _native().fit_backward(x, y, offsets, degrees, max_degree, grad_coef, ws,
-                               None if plan is None else plan.handle.value, precision, center, scale, solver, basis)
+                               _plan_address(plan), precision, center, scale, solver, basis)
     if r is not None:
         if type(r) is int:
             check(r, "fit_backward")
