@@ -60,6 +60,12 @@ def _plan_address(plan):
     return None if plan is None else plan.handle.value if plan.handle else 0
 
 
+def _results(out, k):
+    """What the native module takes for `out`: k Nones without one; it declines False, in the
+    place of a result that the caller left out."""
+    return (None,) * k if out is None else [False if v is None else v for v in out]
+
+
 def options(degree: int, precision: str = "f64", refine: int = 1, center=None, scale=None,
             solver: str = "gepp", basis: str = "monomial", output_basis: str = "x") -> Options:
     if precision not in _PREC:
@@ -266,7 +272,7 @@ def fit_qr_batched(x, y, offsets, degrees, max_degree: int, center=None, scale=N
                    out=None):
     """Independent fits over CSR segments through the streaming QR route;
     returns (coef [B, stride], status [B], sse [B], ws)."""
-    oc, os_, oe = (None, None, None) if out is None else out
+    oc, os_, oe = _results(out, 3)
     r = _native().fit_qr_batched(x, y, offsets, degrees, max_degree, center, scale, coef_stride, ws, oc, os_, oe,
                                  "f64", 0, "gepp", "monomial")
     if r is not None:
@@ -430,7 +436,7 @@ def fit_batched(x, y, offsets, degrees, max_degree: int, precision: str = "f64",
     output_basis="x_and_t" (monomial basis): each row is [a_0..a_M | b_0..b_M | c | s]
     (M = max_degree, stride 2M + 4 by default): the x-basis coefficients, the
     t-basis coefficients of t = (x - c)/s and the fit's c and s."""
-    oc, os_ = (None, None) if out is None else out
+    oc, os_ = _results(out, 2)
     r = _native().fit_batched(x, y, offsets, degrees, max_degree, precision, refine, center, scale,
                               _plan_address(plan), coef_stride, ws, oc, os_, solver, basis, output_basis)
     if r is not None:

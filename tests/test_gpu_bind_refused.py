@@ -54,3 +54,16 @@ def test_closed_plan(monkeypatch, batch):
     plan.close()
     refused(monkeypatch, lambda: lf.fit_batched(*batch, 2, plan=plan), _lib.WORKSPACE)
     refused(monkeypatch, lambda: lf.fit_backward(*batch, 2, torch.ones_like(coef), plan=plan), _lib.WORKSPACE)
+
+
+def test_results_left_out(monkeypatch, batch):
+    """out without its tensors is refused, not taken for no out; the QR batch may leave its sse out."""
+    coef, status, _ = lf.fit_batched(*batch, 2)
+    for out in ((None, None), (coef, None), (None, status)):
+        refused(monkeypatch, lambda: lf.fit_batched(*batch, 2, out=out), _lib.INVALID_ARG)
+    for out in ((None, None, None), (coef, None, None), (None, status, None)):
+        refused(monkeypatch, lambda: lf.fit_qr_batched(*batch, 2, out=out), _lib.INVALID_ARG)
+    qr, _, sse, _ = lf.fit_qr_batched(*batch, 2)
+    got = lf.fit_qr_batched(*batch, 2, out=(coef, status, None))
+    torch.cuda.synchronize()
+    assert got[2] is None and torch.equal(got[0], qr) and (status == 0).all() and torch.isfinite(sse).all()
