@@ -55,8 +55,7 @@ Layout layout(int64_t B, int maxM, int64_t W) {
     L.part = off;
     // the slots may also hold streaming QR factors (fit_qr, degree <= LSEFIT_MAX_DEGREE)
     const int per = (maxM <= LSEFIT_MAX_DEGREE && qr_len(maxM) > nacc(maxM)) ? qr_len(maxM) : nacc(maxM);
-    // (and, after a single fit's sums, the block pairs of the Chebyshev range pass)
-    off = align_up(off + sizeof(double) * ((size_t)(W + B) * per + 2 * (size_t)W));
+    off = align_up(off + sizeof(double) * (size_t)(W + B) * per);
     L.block_tot = off;
     off = align_up(off + sizeof(int64_t) * (size_t)((B + kPlanThreads - 1) / kPlanThreads));
     L.total = off + kAlign;   // slack for aligning the caller's base pointer
@@ -502,14 +501,33 @@ size_t lsefit_workspace_bytes(int64_t batch, int32_t max_degree, const lsefit_sc
 
 int64_t grid_blocks(const Launch& L) { return L.waves / L.wpb; }
 
+// The launch shape of a single Chebyshev fit whose range comes from the data.  The
+// block pairs of its range pass lie past the per-block sums, nacc + 2 doubles a block,
+// inside the slots of one wave each: with a block of several waves by itself, with
+// one of a single wave up to degree 8, where a slot also holds a QR factor.  Above
+// that a schedule of one wave per block runs two, so that no workspace grows.
+static_assert([] {
+    for (int m = 1; m <= LSEFIT_MAX_DEGREE; ++m)
+        if (qr_len(m) < nacc(m) + 2) return false;
+    return 2 * nacc(1) >= nacc(1) + 2;
+}());
+Launch range_launch(Launch L, int degree) {
+    if (L.wpb == 1 && degree > LSEFIT_MAX_DEGREE) {
+        L.wpb = 2;
+        L.waves += L.waves % 2;
+    }
+    return L;
+}
+
 // one streaming pass of a single fit (power sums or refinement), then the
 // one-block kernel that sums the block partials and finishes the fit
 lsefit_status single_pass(bool refine_pass, const FitDesc& d, const Work& w, const lsefit_options* opt, int dt,
-                          const void* x, const void* y, const Launch& L, int mis, const Finish& fz, hipStream_t st) {
+                          const void* x, const void* y, Launch L, int mis, const Finish& fz, hipStream_t st) {
     const RangeArg ra{opt->range_mode, opt->center, opt->scale};
     if (chebyshev(opt)) {
         RangeArg rc = ra;
         if (opt->range_mode == LSEFIT_RANGE_AUTO) {
+            L = range_launch(L, opt->degree);
             LSEFIT_TRY(timed(kTimeRange, st,
                              [&] { return launch_range_cheb(d, w, opt->degree, dt, x, L, mis, st); }));
             rc.mode = kRangeFromPairs;

@@ -197,8 +197,8 @@ __device__ inline void minmax_group(const In* __restrict__ x, int64_t lo, int n,
 }
 
 // The block pairs (min, max) of a single fit's range pass, past the K sums per
-// block that the power-sum pass is about to write (the workspace holds both:
-// layout in api.hip), so that every block of that pass can fold them itself
+// block that the power-sum pass is about to write (the slots hold both:
+// range_launch in api.hip), so that every block of that pass can fold them itself
 __device__ inline double* range_pairs(const Work& w, int K, int64_t G) { return w.part + (int64_t)K * G; }
 
 // single fit: one (min, max) pair per block

@@ -55,7 +55,8 @@ struct Work {
     int32_t* pstatus = nullptr;     // [B] status found while building the tile table
     double* rec = nullptr;          // [B * rec_len(M)]
     double* part = nullptr;         // [(W + B) * nacc(M)] per-(wave, fit) partial sums (batched) or
-                                    // per-block partial sums (single fit; [W * max(nacc, qr_len)])
+                                    // per-block partial sums (single fit; [W * max(nacc, qr_len)]), after
+                                    // them the (min, max) of each block of a Chebyshev range pass
     int64_t* block_tot = nullptr;   // [ceil(B / kPlanThreads)] tile totals of the tile-table blocks
     uint64_t* clock = nullptr;      // [2] start and end of this launch (KernelClock); null unless
                                     // launch_timed arms the launch
