@@ -450,7 +450,7 @@ __host__ __device__ constexpr int gram_len(int m) { return 3 * m + 2; }
 
 // The sample's polynomials, orthogonal over it and scaled so that their
 // recurrence is p_(k+1) = ((t - al_k) / ga_k) p_k - p_(k-1) (two multiply-adds
-// per point, as (t - al_k) / ga_k is affine in x), p_1 = t - al_0, and the fit of the
+// per point, as (t - al_k) / ga_k is affine in t), p_1 = t - al_0, and the fit of the
 // sample in them, sum_k de_k p_k.  Orthogonality to p_(k-1) sets
 // ga_k = ga_(k-1) |p_k|^2 / |p_(k-1)|^2.  Every wave computes them from the same
 // samples (those of single_range, which its rule for (c, s) also takes), so they
@@ -531,29 +531,34 @@ struct SampleBasis {
 template <int M>
 struct AccGram {
     double S[M], H[M], R[M + 1], E;
-    double u1[M], u0[M], nd[M + 1];   // (t - al_k) / ga_k = u1 x + u0; -de_k
+    double u1[M], u0[M], nd[M + 1];   // (t - al_k) / ga_k = u1 t + u0; -de_k
+    // t by itself first: its one rounding is t's own, where a coefficient of x that
+    // holds 1 / ga_k would be off by c / s roundings of t (time stamps in seconds over an
+    // hour: 5e-11 in the coefficients)
+    double inv_s, nc;
     __device__ inline void init(const SampleBasis<M>& b) {
 #pragma unroll
         for (int k = 0; k < M; ++k) S[k] = H[k] = 0.0;
 #pragma unroll
         for (int k = 0; k <= M; ++k) R[k] = 0.0;
         E = 0.0;
-        const double inv_s = 1.0 / b.s, nc = -b.c * inv_s;
+        inv_s = 1.0 / b.s;
+        nc = -b.c * inv_s;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
-            const double step = recip(b.ga[k]);
-            u1[k] = inv_s * step;
-            u0[k] = (nc - b.al[k]) * step;
+            u1[k] = recip(b.ga[k]);
+            u0[k] = -b.al[k] * u1[k];
         }
 #pragma unroll
         for (int k = 0; k <= M; ++k) nd[k] = -b.de[k];
     }
     __device__ inline void point(double xv, double yv) {
+        const double t = fma(xv, inv_s, nc);
         double p[M + 1];
         p[0] = 1.0;
-        p[1] = fma(xv, u1[0], u0[0]);
+        p[1] = t + u0[0];   // ga_0 = 1
 #pragma unroll
-        for (int k = 1; k < M; ++k) p[k + 1] = fma(fma(xv, u1[k], u0[k]), p[k], -p[k - 1]);
+        for (int k = 1; k < M; ++k) p[k + 1] = fma(fma(t, u1[k], u0[k]), p[k], -p[k - 1]);
         double r = yv + nd[0];
 #pragma unroll
         for (int k = 1; k <= M; ++k) r = fma(nd[k], p[k], r);
