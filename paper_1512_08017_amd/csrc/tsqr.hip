@@ -9,12 +9,17 @@
 // triangular, D = diag(d), the rotated right side th (Rb b = th solves the
 // fit) and the residual sum of squares e.  Including a row (x; y) of weight w
 // rotates it into the factor column by column:
-//   d' = d_i + w x_i^2,  cb = d_i / d',  sb = w x_i / d',  w <- cb w,
-//   x_k <- x_k - x_i Rb_ik,  Rb_ik <- cb Rb_ik + sb x_k     (k > i, and y/th),
-// and adds w y^2 to e at the end.  Since cb + sb x_i = 1, the second update
-// is Rb_ik + sb x_k' with the already reduced x_k' (one multiply-add).  Two
-// factors merge by including the rows of one, (weight d_i, row Rb_i, right
-// side th_i), into the other.
+//   d' = d_i + w x_i^2,  w <- w d_i / d',
+//   x_k <- x_k - x_i Rb_ik,  Rb_ik <- (d_i Rb_ik + w x_i x_k) / d'   (k > i, old x_k; and y/th),
+// and adds w y^2 to e at the end.  The factor holds U = D Rb (and D th) and 1/d_i in
+// place of Rb, so that an entry of a rotation is two multiply-adds,
+//   x_k <- x_k - (x_i / d_i) U_ik,  U_ik <- U_ik + w x_i x_k,
+// and no term is larger than the sums it stands for.  Updating Rb_ik itself in as many
+// operations, as Rb_ik + s x_k' with the reduced x_k', cancels where d_i is small
+// against w x_i^2, that is where rows of nearly equal t meet others: x in pairs 1e-8
+// apart left the coefficients 1e-9 off at cond(V) = 2, sorted x in eleven clusters
+// 1e-4 wide 1e-11 (so 1e-15).  Two factors merge by including the rows of one,
+// (weight d_i, row Rb_i, right side th_i), into the other.
 //
 // A single fit large enough for it (qr_sampled in api.hip) first tries a shorter route to the
 // same R and solution, a Cholesky factorisation of a Gram matrix that is near
@@ -44,32 +49,22 @@ __device__ inline double recip(double v) {
 
 template <int N>
 struct GivensQR {
-    static constexpr int NR = N * (N - 1) / 2;   // strict upper part of Rb, packed by rows
+    static constexpr int NR = N * (N - 1) / 2;   // strict upper part, packed by rows
     static constexpr int LEN = 2 * N + NR + 1;   // flat: d, th, Rb, e
-    double d[N], th[N], r[NR > 0 ? NR : 1], e;
+    double d[N], iv[N];                          // iv_i = 1/d_i, 0 while d_i is
+    double uy[N], u[NR > 0 ? NR : 1], e;         // D th and D Rb
 
     __device__ inline void zero() {
 #pragma unroll
-        for (int i = 0; i < N; ++i) d[i] = th[i] = 0.0;
+        for (int i = 0; i < N; ++i) d[i] = iv[i] = uy[i] = 0.0;
 #pragma unroll
-        for (int k = 0; k < NR; ++k) r[k] = 0.0;
+        for (int k = 0; k < NR; ++k) u[k] = 0.0;
         e = 0.0;
     }
-    // offset of Rb_(i, i+1) in r
+    // offset of U_(i, i+1) in u
     static constexpr int row_at(int i) { return i * N - i * (i + 1) / 2; }
-
-    // one entry of a rotation.  v' = v - x r, r' = c r + s v = r + s v': the last
-    // form is one operation shorter, and exact enough while c is not small.  Where a
-    // row of real size meets one that holds only the rounding of equal t (c near 0,
-    // r up to 1/eps), r + s v' cancels r's digits with everything that came in: the
-    // guarded form, which such rows go through, takes c r + s v
-    template <bool GUARD>
-    static __device__ inline void rotate(double xi, double cb, double sb, double& v, double& r) {
-        const double old = v;
-        v = fma(-xi, r, v);
-        if constexpr (GUARD) r = fma(cb, r, sb * old);
-        else r = fma(sb, v, r);
-    }
+    __device__ inline double rb(int i, int k) const { return u[row_at(i) + k - i - 1] * iv[i]; }
+    __device__ inline double th(int i) const { return uy[i] * iv[i]; }
 
     // include the row (x; y) of weight w whose entries before column S are zero.
     // GUARD = false when every d_i (i >= S) is already positive: then
@@ -84,32 +79,33 @@ struct GivensQR {
             const double wxi = w * xi;
             const double dpi = fma(wxi, xi, di);
             const bool nz = !GUARD || dpi != 0.0;
-            const double inv = nz ? recip(dpi) : 0.0;
-            const double cb = nz ? di * inv : 1.0;
-            const double sb = wxi * inv;
-            w *= cb;
+            const double g = xi * iv[i];
+            iv[i] = nz ? recip(dpi) : 0.0;
+            w *= nz ? di * iv[i] : 1.0;
             d[i] = dpi;
 #pragma unroll
             for (int k = i + 1; k < N; ++k) {
-                double& rik = r[row_at(i) + k - i - 1];
-                rotate<GUARD>(xi, cb, sb, x[k], rik);
+                double& uik = u[row_at(i) + k - i - 1];
+                const double old = x[k];
+                x[k] = fma(-g, uik, old);
+                uik = fma(wxi, old, uik);
             }
-            rotate<GUARD>(xi, cb, sb, y, th[i]);
+            const double old = y;
+            y = fma(-g, uy[i], old);
+            uy[i] = fma(wxi, old, uy[i]);
+            // degrees 7 and 8: the scheduler keeps to one column, else the live values of
+            // several exceed the registers (a fit left to the rotations, degree 8: 127 us, else 158)
+            if constexpr (N >= 8) __builtin_amdgcn_sched_barrier(0);
         }
         e = fma(w * y, y, e);
     }
 
-    // every d_i of columns 1.. above what rounding leaves there when all t are equal
-    // (some (8 eps)^2 = 2^-98 of d_0 t^2i, t2 the largest t^2 so far): from then on
-    // data rows need neither the zero-weight guard nor the guarded rotation
-    __device__ inline bool settled(double t2) const {
+    // every d_i of columns 1.. positive (d_0 counts the rows, so it is too
+    // once one row is in): from then on data rows need no zero-weight guard
+    __device__ inline bool settled() const {
         bool ok = true;
-        double floor = d[0] * 0x1p-80;
 #pragma unroll
-        for (int i = 1; i < N; ++i) {
-            floor *= t2;
-            ok = ok && d[i] > floor;
-        }
+        for (int i = 1; i < N; ++i) ok = ok && d[i] > 0.0;
         return ok;
     }
 
@@ -120,23 +116,21 @@ struct GivensQR {
     template <bool GUARD = true, bool TABLE = false>
     __device__ inline void include_data(double (&x)[N], double y, const double* tab = nullptr) {
         const double dp = d[0] + 1.0;
-        double inv;
-        if constexpr (TABLE) inv = tab[(int)d[0]];
-        else inv = recip(dp);
-        const double w = d[0] * inv;
+        const double g = iv[0];
+        if constexpr (TABLE) iv[0] = tab[(int)d[0]];
+        else iv[0] = recip(dp);
+        const double w = d[0] * iv[0];
         d[0] = dp;
 #pragma unroll
         for (int k = 1; k < N; ++k) {
-            double& r0k = r[k - 1];
-            x[k] -= r0k;
-            r0k = fma(inv, x[k], r0k);
+            double& u0k = u[k - 1];
+            const double old = x[k];
+            x[k] = fma(-g, u0k, old);
+            u0k += old;
         }
-        y -= th[0];
-        th[0] = fma(inv, y, th[0]);
-        include_from1<GUARD>(w, x, y);
-    }
-    template <bool GUARD = true>
-    __device__ inline void include_from1(double w, double (&x)[N], double y) {
+        const double old = y;
+        y = fma(-g, uy[0], old);
+        uy[0] += old;
         if constexpr (N > 1) include<1, GUARD>(w, x, y);
         else e = fma(w * y, y, e);
     }
@@ -168,11 +162,11 @@ struct GivensQR {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             if (j == i) v = d[i];
-            if (j == N + i) v = th[i];
-        }
+            if (j == N + i) v = th(i);
 #pragma unroll
-        for (int k = 0; k < NR; ++k)
-            if (j == 2 * N + k) v = r[k];
+            for (int k = i + 1; k < N; ++k)
+                if (j == 2 * N + row_at(i) + k - i - 1) v = rb(i, k);
+        }
         return v;
     }
 };
@@ -194,8 +188,7 @@ struct AccQR {
     static constexpr int N = M + 1;
     GivensQR<N> q;
     double inv_s, nc;
-    double t2 = 0.0;        // largest t^2 of the lane until its factor has settled
-    bool settled = false;   // (d_i only grow, so once it has, it stays so)
+    bool settled = false;   // q.settled() (d_i only grow, so once true it stays true)
     const double* tab;   // kRecipRows reciprocals 1/(j+1) in LDS (fill_recip_rows)
     __device__ inline void init(double c, double is, const double* t) {
         q.zero();
@@ -217,8 +210,8 @@ struct AccQR {
 #pragma unroll
         for (int e = 0; e < VW; ++e) point<GUARD, TABLE>((double)xv[e], (double)yv[e]);
     }
-    // a lane whose factor has settled (after its first N rows or so, unless
-    // its t stay equal) takes the rows without the zero-weight selects, and
+    // a lane whose factor has settled (after its first N distinct points or
+    // so) takes the rows without the zero-weight selects, and
     // while its row count stays inside the table, the first column's
     // reciprocals from it
     template <typename V, int VW>
@@ -228,12 +221,7 @@ struct AccQR {
             else rows<false, false, V, VW>(xv, yv);
         } else {
             rows<true, false, V, VW>(xv, yv);
-#pragma unroll
-            for (int e = 0; e < VW; ++e) {
-                const double t = fma((double)xv[e], inv_s, nc);
-                t2 = fmax(t2, t * t);
-            }
-            settled = q.settled(t2);
+            settled = q.settled();
         }
     }
     __device__ inline void scalar(double xv, double yv) { point(xv, yv); }
@@ -242,23 +230,24 @@ struct AccQR {
 // lanes 0 .. 63 -> lane 0: at each level lane l < off merges the factor of lane
 // l + off, row by row; the senders (lanes >= off) do not change during the
 // level, and every lane takes part in the shuffles.  Fixed order, so the
-// result is reproducible.
+// result is reproducible.  A loop over the levels: unrolled, the six of degree 8 were too
+// much code to inline and the factor went through scratch memory (65,536 fits of 64
+// points 5.2 ms, 1.2 as a loop; no lower degree is slower).
 template <int N, int LANES = kWave>
 __device__ inline void wave_merge(GivensQR<N>& q) {
-    using Q = GivensQR<N>;
     const int lane = lane_id() % LANES;   // LANES < 64: within each group of that many lanes
-#pragma unroll
+#pragma unroll 1
     for (int off = LANES / 2; off >= 1; off >>= 1) {
         const bool recv = lane < off;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const double wi = __shfl_down(q.d[i], off, kWave);
-            const double yi = __shfl_down(q.th[i], off, kWave);
+            const double yi = __shfl_down(q.th(i), off, kWave);
             double x[N];
 #pragma unroll
             for (int k = 0; k < N; ++k) x[k] = k == i ? 1.0 : 0.0;
 #pragma unroll
-            for (int k = i + 1; k < N; ++k) x[k] = __shfl_down(q.r[Q::row_at(i) + k - i - 1], off, kWave);
+            for (int k = i + 1; k < N; ++k) x[k] = __shfl_down(q.rb(i, k), off, kWave);
             if (recv) q.include_row(i, wi, x, yi);
         }
         const double eo = __shfl_down(q.e, off, kWave);
@@ -328,11 +317,11 @@ __device__ inline int qr_solve_store(const GivensQR<N>& q, int64_t npts, double 
     double dmax = 0.0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        finite = finite && isfinite(q.d[i]) && isfinite(q.th[i]);
+        finite = finite && isfinite(q.d[i]) && isfinite(q.uy[i]);
         dmax = fmax(dmax, q.d[i]);
     }
 #pragma unroll
-    for (int k = 0; k < GivensQR<N>::NR; ++k) finite = finite && isfinite(q.r[k]);
+    for (int k = 0; k < GivensQR<N>::NR; ++k) finite = finite && isfinite(q.u[k]);
     if (!finite) st = LSEFIT_ERR_NONFINITE;
     const double tiny = ldexp(dmax, -80);
 #pragma unroll
@@ -341,10 +330,10 @@ __device__ inline int qr_solve_store(const GivensQR<N>& q, int64_t npts, double 
     double b[N], a[N];
 #pragma unroll
     for (int i = N - 1; i >= 0; --i) {
-        double acc = q.th[i];
+        double acc = q.uy[i];
 #pragma unroll
-        for (int k = i + 1; k < N; ++k) acc -= q.r[GivensQR<N>::row_at(i) + k - i - 1] * b[k];
-        b[i] = acc;
+        for (int k = i + 1; k < N; ++k) acc -= q.u[GivensQR<N>::row_at(i) + k - i - 1] * b[k];
+        b[i] = acc * q.iv[i];
     }
     if (st == LSEFIT_OK) {
         to_x_basis<N>(b, c, s, a);
@@ -789,8 +778,8 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
 // 184 -> 31 us; 64 points at degree 3 239 -> 66 us; 16 to 256 points at degree 3
 // 257 -> 114 us; 16 to 1,024 and more points unchanged within 2% (4,096 points 71
 // us before and after; 16 to 65,536 points 1.6 ms).  Above degree 4 the factor
-// alone takes the register file (and 208 to 496 bytes of scratch), so there the
-// walk stays one fit at a time, its descriptors read ahead.
+// alone takes most of the register file, so there the walk stays one fit at a
+// time, its descriptors read ahead.
 // 3 waves per SIMD up to degree 4 (4 before): at 4 both loops together left
 // fits of 4,096 points 2 to 7% slower, at 3 they are no slower than before.
 // ---------------------------------------------------------------------------
