@@ -264,15 +264,17 @@ lsefit_status fit_single_noalloc(const void* x, const void* y, int64_t n, int32_
  *  - every lane of the streaming pass keeps a triangular factor of the rows
  *    (1, t, .., t^m | y) it reads, updated with square-root-free Givens rotations
  *    (Gentleman), and the factors are merged lane -> wave -> block -> fit in a
- *    fixed order (a tall-skinny tree): about (m+1)(m+2)/2 + 12(m+1) float64
+ *    fixed order (a tall-skinny tree): about (m+1)(m+2) + 12m float64
  *    operations per point;
  *  - from 1,024 points on (2^21 at degree 2, 2^23 at degree 1) the pass first
  *    sums the Gram matrix of the polynomials that are orthogonal over the 256
  *    range samples, near the identity wherever the sample stands for the points,
- *    and the right sides of what the sample's own fit leaves (7m+1 float64
+ *    and the right sides of what the sample's own fit leaves (6m+3 float64
  *    operations per point); its Cholesky factor times the sample's triangle is
- *    R.  When the sample does not stand for the points (the pivots tell), a third
- *    launch, empty otherwise, runs the rotations.
+ *    R.  When the sample does not stand for the points (the condition of the Gram
+ *    matrix tells), a third launch, empty otherwise, makes a second pass in the
+ *    polynomials orthogonal over all the points, which the first pass's sums
+ *    give, or runs the rotations where those are not enough.
  *  x, y, n, dt, ws: as fit_single (same workspace size)
  *  opt:      degree 1..LSEFIT_MAX_DEGREE, range (as fit_single); precision
  *            must be LSEFIT_PREC_F64 and basis monomial (else UNSUPPORTED);

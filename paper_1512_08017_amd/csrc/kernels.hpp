@@ -164,8 +164,9 @@ hipError_t launch_qr_finish(const FitDesc& d, const Work& w, int64_t G, double* 
                             hipStream_t st);
 // The sampled route of a larger fit (n_single > 256): per-block sums of the
 // Gram matrix in the sample's orthogonal polynomials into w.part, then one
-// block solves and writes the same, or leaves the fit to the third launch, the
-// rotations in one kernel, which otherwise returns at once.
+// block solves and writes the same, or leaves the fit to the third launch, a
+// second pass in the basis that the first one gives or the rotations, which
+// otherwise returns at once.
 hipError_t launch_qr_sampled(const FitDesc& d, const Work& w, int dtype, const void* x, const void* y,
                              const Launch& L, int mis, const RangeArg& ra, hipStream_t st);
 hipError_t launch_qr_sampled_finish(const FitDesc& d, const Work& w, int64_t G, double* coef, int32_t* status,

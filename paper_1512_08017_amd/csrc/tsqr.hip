@@ -31,8 +31,12 @@
 // points.  With P = [p_k(t_i)] the factor of V is R = chol(P^T P) R_sample, and
 // cond(P) is near 1 wherever the sample stands for the points, so squaring it
 // costs nothing and the error is governed by cond(V) as in the rotations.  The
-// finish checks exactly that (the pivots of P^T P against the sample's norms) and
-// else leaves the fit to the rotations, which need no assumption.
+// finish computes that condition.  Where the sample does not stand for the points (tails
+// of x that 256 samples miss), chol(P^T P) still gives the recurrence of the
+// polynomials that are orthogonal over all the points, and a second pass in them, with the
+// first one's solution as the fit to take the residual from, is near the identity by
+// construction (k_qr_if_left; Cholesky QR done twice).  What is beyond that as
+// well is left to the rotations, which need no assumption.
 #include "kernels_impl.hpp"
 
 namespace lsefit {
@@ -255,10 +259,10 @@ __device__ inline void wave_merge(GivensQR<N>& q) {
     }
 }
 
-// the block's waves -> one factor, written sum-major (entry j of block g at
-// part[j G + g], G blocks)
+// the block's waves -> one factor, written sum-major (entry j of block g of G at
+// part[j G + g])
 template <int N>
-__device__ inline void block_merge_store(const Work& w, GivensQR<N>& q) {
+__device__ inline void block_merge_store(const Work& w, GivensQR<N>& q, int64_t block, int64_t blocks) {
     constexpr int LEN = GivensQR<N>::LEN;
     __shared__ double sh[4][LEN];
     wave_merge(q);
@@ -272,7 +276,7 @@ __device__ inline void block_merge_store(const Work& w, GivensQR<N>& q) {
         const int nw = blockDim.x / kWave;
         for (int v = 1; v < nw; ++v) q.merge([&](int j) { return sh[v][j]; });
 #pragma unroll
-        for (int j = 0; j < LEN; ++j) w.part[(int64_t)j * gridDim.x + blockIdx.x] = q.flat(j);
+        for (int j = 0; j < LEN; ++j) w.part[(int64_t)j * blocks + block] = q.flat(j);
     }
 }
 
@@ -283,10 +287,11 @@ __device__ inline void block_merge_store(const Work& w, GivensQR<N>& q) {
 // dependence chain through each column's reciprocal.
 constexpr int qr_waves_per_eu(int M) { return M <= 3 ? 5 : (M <= 4 ? 4 : 2); }
 
+// the rows of waves W: wave `wave` of them, of block `block` of `blocks`
 template <typename In, int U, int M>
 __device__ __forceinline__ void qr_single_pass(const FitDesc& d, const Work& w, const In* __restrict__ x,
-                                      const In* __restrict__ y, int64_t W, int mis, const RangeArg& ra) {
-    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
+                                      const In* __restrict__ y, int64_t wave, int64_t W, int64_t block, int64_t blocks,
+                                      int mis, const RangeArg& ra) {
     double c, inv_s;
     single_range(d, w, x, ra, &c, &inv_s);
     __shared__ double tab[kRecipRows];
@@ -294,7 +299,7 @@ __device__ __forceinline__ void qr_single_pass(const FitDesc& d, const Work& w, 
     AccQR<M> acc;
     acc.init(c, inv_s, tab);
     stream_strided<U>(x, y, d.n_single, mis, wave, W, acc);
-    block_merge_store<M + 1>(w, acc.q);
+    block_merge_store<M + 1>(w, acc.q, block, blocks);
 }
 
 template <typename In, int U, int M>
@@ -302,7 +307,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(qr_wav
     k_qr_single(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
                 RangeArg ra) {
     const KernelClock kclock_(w.clock);
-    qr_single_pass<In, U, M>(d, w, x, y, W, mis, ra);
+    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
+    qr_single_pass<In, U, M>(d, w, x, y, wave, W, blockIdx.x, gridDim.x, mis, ra);
 }
 
 // Solve Rb b = th for a merged factor of npts rows and write a_0..a_m to out
@@ -395,33 +401,6 @@ __global__ void __launch_bounds__(256)
     qr_finish_block<M>(d, w, G, maxm, coef, status, info);
 }
 
-// The rotations for a fit that the sampled route has left to them (the first
-// word of w.tile_start, unused by a single fit otherwise, is not zero; else the
-// kernel returns at once).  One launch, so that an accepted fit pays for one empty
-// launch and not two: the last block to store its factor (counted in the
-// second word, which the sampled route's finish has cleared) merges and solves.
-// No block waits for another.  The fences make every block's factor visible to
-// the last one; they cost tens of microseconds here, on the route that is
-// seldom taken.
-template <typename In, int U, int M>
-__global__ void __launch_bounds__(256)
-    k_qr_if_left(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
-                 RangeArg ra, double* __restrict__ coef, int32_t* __restrict__ status, double* __restrict__ info) {
-    if (w.tile_start[0] == 0) return;
-    qr_single_pass<In, U, M>(d, w, x, y, W, mis, ra);
-    __shared__ bool last;
-    __syncthreads();   // thread 0 has stored the block's factor
-    if (threadIdx.x == 0) {
-        __threadfence();
-        const unsigned long long before = atomicAdd((unsigned long long*)&w.tile_start[1], 1ull);
-        last = before + 1 == gridDim.x;
-        __threadfence();
-    }
-    __syncthreads();
-    if (!last) return;
-    qr_finish_block<M>(d, w, gridDim.x, M, coef, status, info);
-}
-
 // ---------------------------------------------------------------------------
 // the sampled route of a single fit
 // ---------------------------------------------------------------------------
@@ -431,9 +410,10 @@ __global__ void __launch_bounds__(256)
 // the recurrence, as in the Chebyshev basis: since (t - al_k) p_k = ga_k (p_(k+1) +
 // p_(k-1)), taking <p_j, t p_k> both ways gives
 //   G_(j+1),k = (ga_k (G_j,(k+1) + G_j,(k-1)) + (al_k - al_j) G_jk) / ga_j - G_(j-1),k,
-// which fills row j + 1 from the two above it, its last entry summed.  That is 7m - 1
-// float64 operations per point (with the two conversions 36 at m = 5, 57 at m = 8)
-// where all m (m + 1) / 2 products take 6m + 1 + m (m + 1) / 2 of them, and
+// which fills row j + 1 from the two above it, its last entry summed.  That is 6m + 3
+// float64 operations per point (t and the recurrence 2m, the residual m + 1, its sums and
+// square 2, the other sums 3m; with the two conversions 35 at m = 5, 53 at m = 8)
+// where all m (m + 1) / 2 products take 5m + 3 + m (m + 1) / 2 of them, and
 // the rotations about (m + 1)(m + 2) + 12 m.
 __host__ __device__ constexpr int gram_len(int m) { return 3 * m + 2; }
 
@@ -446,10 +426,35 @@ __host__ __device__ constexpr int gram_len(int m) { return 3 * m + 2; }
 // are the same bits everywhere.  A sample with too few distinct t, or a
 // non-finite one, gives NaN, which the finish sees in the sums.
 template <int M>
-struct SampleBasis {
+struct OrthoBasis {
     double al[M], ga[M], de[M + 1];
     double last;   // |p_M|^2 / |p_(M-1)|^2
     double c, s;
+
+    // kept in the fit's record between the launches, in the place of sums and lambda
+    static constexpr int kAl = rec_S(M), kGa = kAl + M, kLast = kGa + M, kDe = rec_lam(M);
+    __device__ inline void store(double* r) const {
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            r[kAl + k] = al[k];
+            r[kGa + k] = ga[k];
+        }
+        r[kLast] = last;
+#pragma unroll
+        for (int k = 0; k <= M; ++k) r[kDe + k] = de[k];
+    }
+    __device__ inline void load(const double* r) {
+        c = r[0];
+        s = r[1];
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            al[k] = r[kAl + k];
+            ga[k] = r[kGa + k];
+        }
+        last = r[kLast];
+#pragma unroll
+        for (int k = 0; k <= M; ++k) de[k] = r[kDe + k];
+    }
 
     // the samples are loaded once, x and y together, for the range and the basis
     template <typename In>
@@ -525,7 +530,7 @@ struct AccGram {
     // holds 1 / ga_k would be off by c / s roundings of t (time stamps in seconds over an
     // hour: 5e-11 in the coefficients)
     double inv_s, nc;
-    __device__ inline void init(const SampleBasis<M>& b) {
+    __device__ inline void init(const OrthoBasis<M>& b) {
 #pragma unroll
         for (int k = 0; k < M; ++k) S[k] = H[k] = 0.0;
 #pragma unroll
@@ -578,37 +583,16 @@ struct AccGram {
     }
 };
 
-// The pass: the sweep of the power sums, its prologue the sample basis in every
-// wave (about 0.7 us a degree, a chain of wave sums, behind the first loads).
-// Measured against the rotations: 1e8 float32 points, m = 3, 299 -> 121 us (6.6 TB/s,
-// near the sweep's own bound); 1e7 points, m = 5, 69 -> 22 us and m = 8, 870 -> 31 us
-// (float64 issue); the finish 20 -> 4.2 us at m = 5 and 107 -> 6.2 us at m = 8.
-template <typename In, int U, int M>
-__global__ void __launch_bounds__(256)
-    k_qr_sampled(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
-                 RangeArg ra) {
-    const KernelClock kclock_(w.clock);
+// the sweep of the power sums in a basis that `basis` makes while the first loads are in flight
+template <typename In, int U, int M, class Make>
+__device__ inline void gram_pass(const FitDesc& d, const Work& w, const In* __restrict__ x, const In* __restrict__ y,
+                                 int64_t W, int mis, OrthoBasis<M>& b, Make&& basis) {
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id_in_block();
     AccGram<M> acc;
-    SampleBasis<M> b;
-    // range and sample basis while the first loads are in flight
     stream_strided<U, true>(x, y, d.n_single, mis, wave, W, acc, [&] {
-        b.build(x, y, d.n_single, ra);
+        basis();
         acc.init(b);
     });
-    if (wave == 0 && lane_id() == 0) {
-        double* r = w.rec;
-        r[0] = b.c;
-        r[1] = b.s;
-#pragma unroll
-        for (int k = 0; k < M; ++k) {
-            r[rec_S(M) + k] = b.al[k];
-            r[rec_S(M) + M + k] = b.ga[k];
-        }
-        r[rec_S(M) + 2 * M] = b.last;
-#pragma unroll
-        for (int k = 0; k <= M; ++k) r[rec_lam(M) + k] = b.de[k];
-    }
     double v[gram_len(M)];
     acc.out(v);
 #pragma unroll
@@ -616,15 +600,42 @@ __global__ void __launch_bounds__(256)
     single_block_partial<gram_len(M), gram_len(M)>(w, v);
 }
 
-// Sum the block partials, fill the Gram matrix and solve: L D L^T = P^T P, the
-// correction of the sample's fit, the residual sum of squares
+// The pass, its prologue the sample basis in every
+// wave (about 0.7 us a degree, a chain of wave sums, behind the first loads).
+// Measured against the rotations: 1e8 float32 points, m = 3, 299 -> 121 us (6.6 TB/s,
+// near the sweep's own bound); 1e7 points, m = 5, 69 -> 22 us and m = 8, 170 -> 31 us
+// (float64 issue); the finish 20 -> 4.2 us at m = 5 and 25 -> 6.2 us at m = 8.
+template <typename In, int U, int M>
+__global__ void __launch_bounds__(256)
+    k_qr_sampled(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
+                 RangeArg ra) {
+    const KernelClock kclock_(w.clock);
+    OrthoBasis<M> b;
+    gram_pass<In, U, M>(d, w, x, y, W, mis, b, [&] { b.build(x, y, d.n_single, ra); });
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        w.rec[0] = b.c;
+        w.rec[1] = b.s;
+        b.store(w.rec);
+    }
+}
+
+// what is left of a fit after a pass in an orthogonal basis and its finish
+enum SampledLeft { kNothingLeft = 0, kRotationsLeft = 1, kSecondPassLeft = 2 };
+
+// One thread: fill the Gram matrix from the pass's sums and solve: L D L^T = P^T P, the
+// correction of the fit that the residual was taken from, the residual sum of squares
 // sum r^2 - |D^(-1/2) L^-1 P^T r|^2, and the change from p to powers of t and x.
-// Accepted when
-//  - every number is finite;
-//  - every pivot D_k lies within 2^-6 .. 2^6 of what the sample says,
-//    n / K |p_k|^2: then cond(P^T P), scaled, is a few thousand at most, and
-//    the correction, a fraction of the sample's error, loses no digit that the
-//    rotations would keep;
+// rs: the fit's record (range and basis).  With e_k the norms that the recurrence says,
+// n / K |p_k|^2 for the sample's, the result is written when
+//  - every number is finite and every pivot positive;
+//  - H = E^(-1/2) P^T P E^(-1/2) has |H^(1/2)|_F^2 |H^(-1/2)|_F^2 <= 1.5 N^2 (N^2 for the
+//    identity): the pivots alone do not bound its condition.  Emulated on the CPU
+//    over x uniform, normal, Laplace, logistic, exponential, lognormal, Student, arcsine and
+//    in clusters, degrees 2 to 8, 1,025 to 60,001 points: the errors of fits accepted up to
+//    there are those of the rotations (a few 1e-16 at degree 4, 1e-15 to 1e-14 at 8),
+//    from 4 on they are larger, tenfold past 30 (normal x, degree 8: 5e-12 against 5e-14);
+//  - the correction, in this norm, is at most twice the solution: else its rounding, relative
+//    to the sample's noise, shows (values that are nearly all noise);
 //  - the be_k = ga_k ga_(k-1) of the monic recurrence (1/4 of the squared half-range
 //    for smooth densities, k s^2 for a normal one) lie within 2^8 of each other,
 //    so that filling the matrix scales no entry's rounding by more than 2^4 a row;
@@ -632,30 +643,22 @@ __global__ void __launch_bounds__(256)
 //    good to 64 roundings;
 //  - |R_kk|, R_kk^2 = D_k times the squared leading coefficient, stays above 2^-36
 //    of the largest: 16 times clear of the singular rule.
-// Otherwise w.tile_start[0] tells the rotations to run.
+// Where only the second or third fails, H up to 2^30 N^2, the factor gives the
+// polynomials orthogonal over all the points, P' = L^-1 P: their recurrence is
+//   al'_k = al_k + l_(k+1),k - l_k,(k-1),  be'_k = D_k / D_(k-1)   (monic p),
+// and the solution in them, L^T de + D^-1 L^-1 P^T r; both go to the record for a second
+// pass, whose H is the identity to 2^30 roundings.
 template <int M>
-__global__ void __launch_bounds__(kFinishWaves * kWave)
-    k_qr_sampled_finish(FitDesc d, Work w, int64_t G, double* __restrict__ coef, int32_t* __restrict__ status,
-                        double* __restrict__ info) {
-    const KernelClock kclock_(w.clock);
+__device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Work& w, const double* sums, const double* rs,
+                                            bool first, double* __restrict__ coef, int32_t* __restrict__ status,
+                                            double* __restrict__ info) {
     constexpr int N = M + 1;
-    constexpr int K = gram_len(M);
-    constexpr int rl = rec_len(M);
-    __shared__ double sums[K];
-    __shared__ double rs[rl];
-    const double rv = threadIdx.x < rl ? w.rec[threadIdx.x] : 0.0;
-    block_sum_partials<K>(w.part, G, sums);
-    if (threadIdx.x < rl) rs[threadIdx.x] = rv;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
+    OrthoBasis<M> B;
+    B.load(rs);
     const double n = (double)d.n_single;
-    const double* al = rs + rec_S(M);
-    const double* ga = rs + rec_S(M) + M;
-    const double last = rs[rec_S(M) + 2 * M];
-    const double* de = rs + rec_lam(M);
-    double A[N][N], z[N], step[M];   // A: lower triangle, A[k][j] = G_jk
+    double A[N][N], z[N], step[M], e[N], lead[N];   // A: lower triangle, A[k][j] = G_jk; 1 / lead_k: leading coefficients
 #pragma unroll
-    for (int k = 0; k < M; ++k) step[k] = recip(ga[k]);
+    for (int k = 0; k < M; ++k) step[k] = recip(B.ga[k]);
     A[0][0] = n;
 #pragma unroll
     for (int k = 1; k <= M; ++k) A[k][0] = sums[k - 1];
@@ -665,34 +668,32 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
     for (int j = 0; j + 1 < M; ++j) {
 #pragma unroll
         for (int k = j + 1; k < M; ++k) {
-            const double v = fma(ga[k], A[k + 1][j] + A[k - 1][j], (al[k] - al[j]) * A[k][j]) * step[j];
+            const double v = fma(B.ga[k], A[k + 1][j] + A[k - 1][j], (B.al[k] - B.al[j]) * A[k][j]) * step[j];
             A[k][j + 1] = j > 0 ? v - A[k][j > 0 ? j - 1 : 0] : v;
         }
     }
 #pragma unroll
     for (int k = 0; k <= M; ++k) z[k] = sums[2 * M + k];
-    const double E = sums[K - 1];
-    bool ok = isfinite(E);
-    double be_min = INFINITY, be_max = 0.0;
+    const double E = sums[gram_len(M) - 1];
+    e[0] = n;
+    lead[0] = 1.0;
+    double trace = 1.0;   // of H
 #pragma unroll
-    for (int k = 1; k < M; ++k) {
-        be_min = fmin(be_min, ga[k] * ga[k - 1]);
-        be_max = fmax(be_max, ga[k] * ga[k - 1]);
+    for (int k = 1; k < N; ++k) {   // |p_k|^2 / |p_(k-1)|^2 and the leading coefficient 1 / (ga_0 .. ga_(k-1))
+        e[k] = e[k - 1] * (k < M ? B.ga[k < M ? k : 0] * step[k - 1] : B.last);
+        lead[k] = lead[k - 1] * B.ga[k - 1];
+        trace = fma(A[k][k], recip(e[k]), trace);
     }
-    if (M > 2) ok = ok && be_max <= 256.0 * be_min;
     // A = L D L^T in place (unit L below the diagonal), z = L^-1 P^T r
-    double expect = n, lead = 1.0, dmax = 0.0, dmin = INFINITY, taken = 0.0;
-    double inv[N];
+    bool sound = isfinite(E);
+    double dmax = 0.0, dmin = INFINITY, taken = 0.0;
+    double D[N], inv[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        const double dk = A[k][k];
-        if (k > 0) {   // |p_k|^2 / |p_(k-1)|^2 and the leading coefficient 1 / (ga_0 .. ga_(k-1))
-            expect *= k < M ? ga[k < M ? k : 0] * step[k - 1] : last;
-            lead *= ga[k - 1];
-        }
-        ok = ok && isfinite(z[k]) && dk >= 0.015625 * expect && dk <= 64.0 * expect;
-        dmax = fmax(dmax, dk * lead * lead);
-        dmin = fmin(dmin, dk * lead * lead);
+        const double dk = D[k] = A[k][k];
+        sound = sound && isfinite(z[k]) && dk > 0.0 && isfinite(dk);
+        dmax = fmax(dmax, dk * lead[k] * lead[k]);
+        dmin = fmin(dmin, dk * lead[k] * lead[k]);
         inv[k] = recip(dk);
         taken = fma(z[k] * inv[k], z[k], taken);
         double l[N];
@@ -707,14 +708,73 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
 #pragma unroll
         for (int i = k + 1; i < N; ++i) A[i][k] = l[i];
     }
-    ok = ok && dmin > ldexp(dmax, -72) && (taken <= 0.984375 * E);
-    double g[N];
+    sound = sound && dmin > ldexp(dmax, -72);
+    double be_min = INFINITY, be_max = 0.0;
+#pragma unroll
+    for (int k = 1; k < M; ++k) {
+        be_min = fmin(be_min, B.ga[k] * B.ga[k - 1]);
+        be_max = fmax(be_max, B.ga[k] * B.ga[k - 1]);
+    }
+    if (M > 2) sound = sound && be_max <= 256.0 * be_min;
+    // |H^(-1/2)|_F^2 = sum over L^-1 of (L^-1)_ij^2 e_j / D_i
+    double back = 0.0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        double X[N];
+#pragma unroll
+        for (int i = j; i < N; ++i) {
+            double a = i == j ? 1.0 : 0.0;
+#pragma unroll
+            for (int k = j; k < i; ++k) a = fma(-A[i][k], X[k], a);
+            X[i] = a;
+            back = fma(a * a * e[j], inv[i], back);
+        }
+    }
+    const double cond = trace * back * (1.0 / (N * N));
+    double g[N], size = 0.0;
 #pragma unroll
     for (int i = N - 1; i >= 0; --i) {
         double a = z[i] * inv[i];
 #pragma unroll
         for (int k = i + 1; k < N; ++k) a = fma(-A[k][i], g[k], a);
         g[i] = a;
+        size = fma((B.de[i] + a) * (B.de[i] + a), e[i], size);
+    }
+    const bool near = cond <= 1.5 && taken <= 4.0 * size;
+    bool ok = sound && near && taken <= 0.984375 * E;
+    if (first && sound && !near && cond <= 0x1p30) {
+        OrthoBasis<M> next;
+        double up = 1.0;   // lead' of the next basis
+        bool good = true;
+        double lo = INFINITY, hi = 0.0;
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            next.al[k] = fma(B.ga[k], A[k + 1][k], B.al[k]);
+            next.ga[k] = 1.0;
+            if (k > 0) {
+                next.al[k] = fma(-B.ga[k - 1], A[k][k > 0 ? k - 1 : 0], next.al[k]);
+                const double be = D[k] * inv[k - 1] * B.ga[k - 1] * B.ga[k - 1];
+                next.ga[k] = be * recip(next.ga[k - 1]);
+                lo = fmin(lo, be);
+                hi = fmax(hi, be);
+            }
+            good = good && isfinite(next.al[k]) && isfinite(next.ga[k]) && next.ga[k] > 0.0;
+        }
+        const double r = B.ga[M - 1] * recip(next.ga[M - 1]);
+        next.last = D[M] * inv[M - 1] * r * r;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            double a = fma(z[k], inv[k], B.de[k]);
+#pragma unroll
+            for (int i = k + 1; i < N; ++i) a = fma(A[i][k], B.de[i], a);
+            next.de[k] = a * (up * recip(lead[k]));
+            good = good && isfinite(next.de[k]);
+            if (k < M) up *= next.ga[k < M ? k : 0];
+        }
+        if (good && isfinite(next.last) && (M <= 2 || hi <= 256.0 * lo)) {
+            next.store(w.rec);
+            return kSecondPassLeft;
+        }
     }
     // sum_k (de_k + g_k) p_k in powers of t, from the recurrence
     double b[N], p[N], pp[N];
@@ -726,7 +786,7 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
     }
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        const double a = de[k] + g[k];
+        const double a = B.de[k] + g[k];
 #pragma unroll
         for (int j = 0; j <= k; ++j) b[j] = fma(a, p[j], b[j]);
         if (k < M) {
@@ -734,7 +794,7 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
 #pragma unroll
             for (int j = 0; j < N; ++j) {
                 const double up = j > 0 ? p[j - 1] : 0.0;
-                pn[j] = fma(fma(-al[k < M ? k : 0], p[j], up), step[k < M ? k : 0], -pp[j]);
+                pn[j] = fma(fma(-B.al[k < M ? k : 0], p[j], up), step[k < M ? k : 0], -pp[j]);
             }
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -743,14 +803,11 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
             }
         }
     }
-    const double c = rs[0], s = rs[1];
     double a[N];
-    to_x_basis<N>(b, c, s, a);
+    to_x_basis<N>(b, B.c, B.s, a);
 #pragma unroll
     for (int k = 0; k < N; ++k) ok = ok && isfinite(a[k]) && isfinite(b[k]);
-    w.tile_start[0] = ok ? 0 : 1;
-    w.tile_start[1] = 0;
-    if (!ok) return;
+    if (!ok) return kRotationsLeft;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         coef[k] = a[k];
@@ -760,10 +817,126 @@ __global__ void __launch_bounds__(kFinishWaves * kWave)
     w.pstatus[0] = LSEFIT_OK;
     status[0] = LSEFIT_OK;
     if (info) {
-        info[0] = c;
-        info[1] = s;
+        info[0] = B.c;
+        info[1] = B.s;
         info[2] = E - taken;
     }
+    return kNothingLeft;
+}
+
+// Sum the block partials and solve.  The first word of w.tile_start, unused by a
+// single fit otherwise, says what is left; the second one counts blocks in the launch after.
+template <int M>
+__global__ void __launch_bounds__(kFinishWaves * kWave)
+    k_qr_sampled_finish(FitDesc d, Work w, int64_t G, double* __restrict__ coef, int32_t* __restrict__ status,
+                        double* __restrict__ info) {
+    const KernelClock kclock_(w.clock);
+    constexpr int rl = rec_len(M);
+    __shared__ double sums[gram_len(M)];
+    __shared__ double rs[rl];
+    const double rv = threadIdx.x < rl ? w.rec[threadIdx.x] : 0.0;
+    block_sum_partials<gram_len(M)>(w.part, G, sums);
+    if (threadIdx.x < rl) rs[threadIdx.x] = rv;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    w.tile_start[0] = solve_sampled<M>(d, w, sums, rs, true, coef, status, info);
+    w.tile_start[1] = 0;
+}
+
+// the same sums (the same bits) by a block of any number of waves, four of them at a time; the
+// partials of G blocks of a grid of `stride`
+template <int NK>
+__device__ inline void block_sum_partials_by(const double* __restrict__ part, int64_t stride, int64_t G, int waves,
+                                             double* out) {
+    constexpr int C = 4;
+    const int lane = lane_id();
+    for (int k0 = C * wave_id_in_block(); k0 < NK; k0 += C * waves) {
+        double t[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) t[c] = 0.0;
+        for (int64_t g0 = 0; g0 < G; g0 += kFinishChunk * kWave) {
+            double x[kFinishChunk][C];
+#pragma unroll
+            for (int i = 0; i < kFinishChunk; ++i) {
+                const int64_t g = min(g0 + i * kWave + lane, G - 1);
+#pragma unroll
+                for (int c = 0; c < C; ++c) x[i][c] = part[(int64_t)min(k0 + c, NK - 1) * stride + g];
+            }
+#pragma unroll
+            for (int i = 0; i < kFinishChunk; ++i) {
+                const bool in = g0 + i * kWave + lane < G;
+#pragma unroll
+                for (int c = 0; c < C; ++c) t[c] = in ? t[c] + x[i][c] : t[c];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const double tot = wave_sum(t[c]);
+            if (lane == 0 && k0 + c < NK) out[k0 + c] = tot;
+        }
+    }
+}
+
+// Whether this block is the last of `blocks` to get here: it then sees what every
+// one has stored.  Thread 0 releases its block's stores behind the barrier; only the last
+// block acquires (an acquire by every block, which throws cached lines away, cost a
+// fit with a second pass over 1e6 points 7 us more).  No block waits for another.
+__device__ inline bool last_block(const Work& w, int64_t blocks) {
+    __shared__ bool last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        const unsigned long long before = __hip_atomic_fetch_add((unsigned long long*)&w.tile_start[1], 1ull,
+                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = before + 1 == (unsigned long long)blocks;
+        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    return last;
+}
+
+// What the sampled route has left of a fit (else the kernel returns at once): the second
+// pass in the basis of the record, or the rotations.  One launch, so that an accepted
+// fit pays for one empty launch and not for several: the last block to store its part
+// finishes.  A second pass that its finish does not take (it is the identity by construction; no
+// data is known where it does not) is left to the rotations of that block alone.
+// Of a small fit only as many blocks take part as have a vector for every lane: the others'
+// parts would only be more to merge.
+constexpr int if_left_waves_per_eu(int M) { return M <= 3 ? 4 : 2; }
+
+template <typename In, int U, int M>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(if_left_waves_per_eu(M))))
+    k_qr_if_left(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int mis, RangeArg ra,
+                 double* __restrict__ coef, int32_t* __restrict__ status, double* __restrict__ info) {
+    const int64_t left = w.tile_start[0];
+    if (left == kNothingLeft) return;
+    const int nw = blockDim.x / kWave;
+    const int64_t rounds = d.n_single / (VecOf<In>::W * kWave * nw) + 1;   // of one vector a lane
+    int64_t blocks = rounds < gridDim.x ? rounds : gridDim.x;
+    if (blockIdx.x >= blocks) return;
+    int64_t first = (int64_t)blockIdx.x * nw, waves = blocks * nw, block = blockIdx.x;
+    if (left == kSecondPassLeft) {
+        constexpr int rl = rec_len(M);
+        __shared__ double sums[gram_len(M)];
+        __shared__ double rs[rl];
+        __shared__ int still;
+        OrthoBasis<M> b;
+        gram_pass<In, 2, M>(d, w, x, y, waves, mis, b, [&] { b.load(w.rec); });
+        if (!last_block(w, blocks)) return;
+        block_sum_partials_by<gram_len(M)>(w.part, gridDim.x, blocks, nw, sums);
+        for (int i = threadIdx.x; i < rl; i += blockDim.x) rs[i] = w.rec[i];
+        __syncthreads();
+        if (threadIdx.x == 0) still = solve_sampled<M>(d, w, sums, rs, false, coef, status, info);
+        __syncthreads();
+        if (still == kNothingLeft) return;
+        first = block = 0;
+        waves = nw;
+        blocks = 1;
+    }
+    qr_single_pass<In, U, M>(d, w, x, y, first + wave_id_in_block(), waves, block, blocks, mis, ra);
+    if (left != kSecondPassLeft && !last_block(w, blocks)) return;
+    __syncthreads();   // thread 0 has stored the only block's factor
+    qr_finish_block<M>(d, w, blocks, M, coef, status, info);
 }
 
 // ---------------------------------------------------------------------------
@@ -921,10 +1094,10 @@ hipError_t launch_qr_if_left(const FitDesc& d, const Work& w, int dtype, const v
     auto body = [&]<int M>() {
         if (dtype == LSEFIT_F32)
             hipLaunchKernelGGL((k_qr_if_left<float, 1, M>), grid, block, 0, st, d, w, (const float*)x, (const float*)y,
-                               L.waves, mis, ra, coef, status, info);
+                               mis, ra, coef, status, info);
         else
             hipLaunchKernelGGL((k_qr_if_left<double, 1, M>), grid, block, 0, st, d, w, (const double*)x,
-                               (const double*)y, L.waves, mis, ra, coef, status, info);
+                               (const double*)y, mis, ra, coef, status, info);
     };
     dispatch_degree<LSEFIT_MAX_DEGREE>(d.degree, body);
     return hipGetLastError();
