@@ -693,7 +693,7 @@ inline bool cheb_lane_finish(int maxm, int64_t batch) {
 }
 
 // Batch of degrees <= MAXC (4 or 8), one fit per thread: the thread sums its fit's partial
-// slots in wave order, forms C_0..C_2M (C_(M+j) = 2 E_j - C_(M-j)) and the Gram
+// slots in wave order (the wave those of a fit with many), forms C_0..C_2M (C_(M+j) = 2 E_j - C_(M-j)) and the Gram
 // system G_jk = (C_(j+k) + C_|j-k|)/2, G c = D, in its registers and solves it
 // (matrix_gepp / matrix_cholesky: the pivot and singular rules of the wave
 // solve).  At these degrees a wave per fit leaves most lanes idle and the
@@ -703,8 +703,10 @@ inline bool cheb_lane_finish(int maxm, int64_t batch) {
 template <int MAXC>
 __global__ void __launch_bounds__(256) k_finish_cheb_lane(FitDesc d, Work w, int64_t W, int maxm, Finish fz) {
     const KernelClock kclock_(w.clock);
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= d.batch) return;
+    // a lane past the last fit holds the last one again and drops it: the whole wave
+    // takes part in the sums of a long fit
+    const int64_t own = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t f = own < d.batch ? own : d.batch - 1;
     // the loads that depend on no other, issued together: status, degree,
     // tile range, point count and the range from the record
     const int pst = w.pstatus[f];
@@ -714,13 +716,10 @@ __global__ void __launch_bounds__(256) k_finish_cheb_lane(FitDesc d, Work w, int
     const int64_t n = fit_hi(d, f) - fit_lo(d, f);
     double* r = w.rec + f * rec_len(maxm);
     const double rc = r[0], rs = r[1];
-    if (pst != LSEFIT_OK) {
-        if (fz.mode != kMomentsOnly) cheb_fail(d, w, f, maxm, fz, pst);
-        return;
-    }
+    const bool sum = own < d.batch && pst == LSEFIT_OK;
     const int stride = nacc(maxm);
-    const int64_t w0 = wave_of_tile(ts, NT, W);
-    const int64_t w1 = wave_of_tile(te - 1, NT, W);
+    const int64_t w0 = sum ? wave_of_tile(ts, NT, W) : 0;
+    const int64_t w1 = sum ? wave_of_tile(te - 1, NT, W) : -1;
     // the sums of the largest degree's count, whatever this fit's degree (a
     // degree-m fit's sums are the first ones of its slots; an index past the
     // slot reads its last sum again), so that the loads sit outside the degree
@@ -729,12 +728,51 @@ __global__ void __launch_bounds__(256) k_finish_cheb_lane(FitDesc d, Work w, int
     double all[KMAX];
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) all[k] = 0.0;
-    for (int64_t wv = w0; wv <= w1; ++wv) {
-        if (!wave_owns_tiles(wv, NT, W)) continue;
-        const double* p = w.part + (wv + f) * stride;
+    // U slots at a time, `step` apart, their loads issued together: one past the last, or of a
+    // wave without tiles, reads the first one again and drops it
+    auto add = [&]<int U>(int64_t wv, int64_t last, int64_t step, int64_t fit) {
+        for (; wv <= last; wv += U * step) {
+            double v[U][KMAX];
+            bool in[U];
 #pragma unroll
-        for (int k = 0; k < KMAX; ++k) all[k] += p[k < stride ? k : stride - 1];
+            for (int u = 0; u < U; ++u) {
+                in[u] = wv + u * step <= last && wave_owns_tiles(wv + u * step, NT, W);
+                const double* p = w.part + ((in[u] ? wv + u * step : wv) + fit) * stride;
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k) v[u][k] = p[k < stride ? k : stride - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k) all[k] = in[u] ? all[k] + v[u][k] : all[k];
+        }
+    };
+    // A fit of more than 64 slots is added up by the whole wave, lane l every 64th slot:
+    // one long fit among 8,192 of 64 points, degree 5, in one thread's chain of loads took
+    // the call from 41 to 320 us (2^22 points) and 750 us (2^24, all 2,048 waves)
+    const bool spread = w1 - w0 >= kWave;
+    for (uint64_t todo = __ballot(spread); todo; todo &= todo - 1) {
+        const int src = __ffsll((unsigned long long)todo) - 1;
+        double mine[KMAX];
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            mine[k] = all[k];
+            all[k] = 0.0;
+        }
+        const int64_t a = bcast_i64(w0, src), b = bcast_i64(w1, src), fit = bcast_i64(f, src);
+        add.template operator()<2>(a + lane_id(), b, kWave, fit);
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const double t = wave_sum(all[k]);
+            all[k] = lane_id() == src ? t : mine[k];
+        }
     }
+    if (own >= d.batch) return;
+    if (pst != LSEFIT_OK) {
+        if (fz.mode != kMomentsOnly) cheb_fail(d, w, f, maxm, fz, pst);
+        return;
+    }
+    if (!spread) add.template operator()<1>(w0, w1, 1, f);
     auto body = [&]<int M>() {
         constexpr int N = M + 1;
         constexpr int K = nacc(M);
