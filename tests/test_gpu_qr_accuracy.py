@@ -98,6 +98,29 @@ def test_nearly_equal_x_in_batches(form, m):
     announce(f"  largest error {worst:.1e}")
 
 
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 6])
+def test_equal_x_in_batches(m, dtype):
+    """x that repeat exactly, with the same gate: roundings times cond(V)."""
+    announce(f"qr batch, equal x, m={m} {np.dtype(dtype).name}")
+    rng = np.random.default_rng(m)
+    xs = [clustered(form, rng, n, 0.0).astype(dtype) for n in (60, 100, 129, 384, 2000, 20_000) for form in FORMS]
+    ys = [values(x.astype(np.float64), m, rng).astype(dtype) for x in xs]
+    off = np.concatenate([[0], np.cumsum([x.size for x in xs])]).astype(np.int64)
+    deg = np.full(len(xs), m, np.int32)
+    coef, status, _, _ = lf.fit_qr_batched(to_dev(np.concatenate(xs)), to_dev(np.concatenate(ys)), to_dev(off),
+                                           to_dev(deg), m, center=0.0, scale=1.0)
+    torch.cuda.synchronize()
+    assert (status.cpu().numpy() == 0).all()
+    coef, worst = coef.cpu().numpy(), 0.0
+    for f, (x, y) in enumerate(zip(xs, ys)):
+        b, kappa, ke = reference(x, y, m, 0.0, 1.0)
+        e = normwise(coef[f, : m + 1], b)
+        worst = max(worst, e / (EPS * kappa * (1.0 + ke)))
+        assert e <= 64 * EPS * kappa * (1.0 + ke), (x.size, FORMS[f % len(FORMS)], e)
+    announce(f"  largest error {worst:.2g} roundings")
+
+
 @pytest.mark.parametrize("m,n", [(1, 5001), (2, 70_001), (3, 999), (6, 1001)])
 def test_nearly_equal_x_in_one_fit(m, n):
     announce(f"qr, nearly equal x, {n} points, m={m}")
