@@ -629,25 +629,27 @@ enum SampledLeft { kNothingLeft = 0, kRotationsLeft = 1, kSecondPassLeft = 2 };
 // n / K |p_k|^2 for the sample's, the result is written when
 //  - every number is finite and every pivot positive;
 //  - H = E^(-1/2) P^T P E^(-1/2) has |H^(1/2)|_F^2 |H^(-1/2)|_F^2 <= 1.5 N^2 (N^2 for the
-//    identity): the pivots alone do not bound its condition.  Emulated on the CPU
+//    identity; 32 N^2 at degree 2, any at degree 1): the pivots alone do not bound its condition.  Emulated on the CPU
 //    over x uniform, normal, Laplace, logistic, exponential, lognormal, Student, arcsine and
 //    in clusters, degrees 2 to 8, 1,025 to 60,001 points: the errors of fits accepted up to
 //    there are those of the rotations (a few 1e-16 at degree 4, 1e-15 to 1e-14 at 8),
-//    from 4 on they are larger, tenfold past 30 (normal x, degree 8: 5e-12 against 5e-14);
+//    from degree 3 on they are larger past 4 N^2, tenfold past 30 N^2 (normal x, degree 8:
+//    5e-12 against 5e-14), at degree 2 past 100 N^2, at degree 1 nowhere;
 //  - the correction, in this norm, is at most twice the solution: else its rounding, relative
 //    to the sample's noise, shows (values that are nearly all noise);
 //  - the be_k = ga_k ga_(k-1) of the monic recurrence (1/4 of the squared half-range
-//    for smooth densities, k s^2 for a normal one) lie within 2^8 of each other,
-//    so that filling the matrix scales no entry's rounding by more than 2^4 a row;
+//    for smooth densities, k s^2 for a normal one) lie within 2^8 of each other in the
+//    sample's basis, so that filling the matrix scales no entry's rounding by more than 2^4 a
+//    row, and within 2^16 in the second pass's, where they grow with k for x with tails;
 //  - the correction takes less than 63/64 of sum r^2: then the difference is
 //    good to 64 roundings;
 //  - |R_kk|, R_kk^2 = D_k times the squared leading coefficient, stays above 2^-36
 //    of the largest: 16 times clear of the singular rule.
-// Where only the second or third fails, H up to 2^30 N^2, the factor gives the
+// Where only the second or third fails, H up to 2^40 N^2, the factor gives the
 // polynomials orthogonal over all the points, P' = L^-1 P: their recurrence is
 //   al'_k = al_k + l_(k+1),k - l_k,(k-1),  be'_k = D_k / D_(k-1)   (monic p),
 // and the solution in them, L^T de + D^-1 L^-1 P^T r; both go to the record for a second
-// pass, whose H is the identity to 2^30 roundings.
+// pass, whose H is the identity to 2^40 roundings or so (emulated, up to 2^49: to 1e-3).
 template <int M>
 __device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Work& w, const double* sums, const double* rs,
                                             bool first, double* __restrict__ coef, int32_t* __restrict__ status,
@@ -715,7 +717,7 @@ __device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Wor
         be_min = fmin(be_min, B.ga[k] * B.ga[k - 1]);
         be_max = fmax(be_max, B.ga[k] * B.ga[k - 1]);
     }
-    if (M > 2) sound = sound && be_max <= 256.0 * be_min;
+    if (M > 2) sound = sound && be_max <= (first ? 0x1p8 : 0x1p16) * be_min;
     // |H^(-1/2)|_F^2 = sum over L^-1 of (L^-1)_ij^2 e_j / D_i
     double back = 0.0;
 #pragma unroll
@@ -740,9 +742,10 @@ __device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Wor
         g[i] = a;
         size = fma((B.de[i] + a) * (B.de[i] + a), e[i], size);
     }
-    const bool near = cond <= 1.5 && taken <= 4.0 * size;
+    constexpr double limit = M == 1 ? 0x1p40 : (M == 2 ? 32.0 : 1.5);
+    const bool near = cond <= limit && taken <= 4.0 * size;
     bool ok = sound && near && taken <= 0.984375 * E;
-    if (first && sound && !near && cond <= 0x1p30) {
+    if (first && sound && !near && cond <= 0x1p40) {
         OrthoBasis<M> next;
         double up = 1.0;   // lead' of the next basis
         bool good = true;
@@ -771,7 +774,7 @@ __device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Wor
             good = good && isfinite(next.de[k]);
             if (k < M) up *= next.ga[k < M ? k : 0];
         }
-        if (good && isfinite(next.last) && (M <= 2 || hi <= 256.0 * lo)) {
+        if (good && isfinite(next.last) && (M <= 2 || hi <= 0x1p16 * lo)) {
             next.store(w.rec);
             return kSecondPassLeft;
         }
