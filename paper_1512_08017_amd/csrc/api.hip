@@ -678,9 +678,10 @@ lsefit_status fit_single_noalloc(const void* x, const void* y, int64_t n, int32_
 // the host's launches are all that counts, the rotations stay ahead (1e6
 // float32 points, m = 1: 18 us against 22; m = 2: 20 against 22; at 4e6 points
 // m = 2 turns to 26 against 22, m = 1 at about 6e6).  From degree 3 on the
-// rotations' merge tree alone costs more than the third launch at every size (20,000
-// points, m = 3: 28 us against 22; m = 8: 290 against 24; 1e7 points, m = 5: 92
-// against 33); the route needs more points than its sample of 256.
+// rotations' merge tree alone costs more than the third launch at every size (1,000
+// points by rotations, 10,000 by the route, m = 3: 25 us against 14; m = 8: 98 against
+// 21; 1e7 points, m = 5: 92 against 36); the route needs more points than its sample
+// of 256.
 bool qr_sampled(int64_t n, int degree) {
     const int64_t from = degree == 1 ? (int64_t)1 << 23 : (degree == 2 ? (int64_t)1 << 21 : 1024);
     return n >= from;

@@ -1,10 +1,10 @@
 // Argument marshalling of the Python surface in native code: the checks, the
 // result tensors and the C-ABI call of fit, fit_qr, residuals, fit_batched,
 // fit_qr_batched and fit_backward in one step each.  A small fit is a few microseconds of GPU
-// work; on the MI355X machine's host a call took 18.3 us with the same steps
-// through ctypes and Python-level tensor calls, and takes 12.6 us with them here
-// (two kernel launches included); the forward and backward of a batch through
-// autograd 132 and 86 us.
+// work; on the MI355X machine's host a call with two kernel launches took 18.3 us
+// with the same steps through ctypes and Python-level tensor calls and 12.6 us
+// with them here (9.5 us where a fit takes one launch); the forward and backward of a
+// batch through autograd 132 and 86 us.
 //
 // Every function takes the calls that need nothing but marshalling (plain
 // GPU tensors of the right types and shapes, known option names) and returns

@@ -282,10 +282,10 @@ __device__ inline void block_merge_store(const Work& w, GivensQR<N>& q, int64_t 
 
 // Every point updates the same factor, so the rounds carry no parallel work
 // worth registers: one vector per round and a register budget (96 VGPRs,
-// 5 waves per SIMD, up to m = 3; 128 and 4 at m = 4; 256 above) keep the
+// 5 waves per SIMD, up to m = 2; 128 and 4 to m = 4; 256 above) keep the
 // compiler from hoisting across points, and the extra waves cover the
 // dependence chain through each column's reciprocal.
-constexpr int qr_waves_per_eu(int M) { return M <= 3 ? 5 : (M <= 4 ? 4 : 2); }
+constexpr int qr_waves_per_eu(int M) { return M <= 2 ? 5 : (M <= 4 ? 4 : 2); }
 
 // the rows of waves W: wave `wave` of them, of block `block` of `blocks`
 template <typename In, int U, int M>
@@ -602,9 +602,9 @@ __device__ inline void gram_pass(const FitDesc& d, const Work& w, const In* __re
 
 // The pass, its prologue the sample basis in every
 // wave (about 0.7 us a degree, a chain of wave sums, behind the first loads).
-// Measured against the rotations: 1e8 float32 points, m = 3, 299 -> 121 us (6.6 TB/s,
-// near the sweep's own bound); 1e7 points, m = 5, 69 -> 22 us and m = 8, 170 -> 31 us
-// (float64 issue); the finish 20 -> 4.2 us at m = 5 and 25 -> 6.2 us at m = 8.
+// Measured against the rotations: 1e8 float32 points, m = 3, 346 -> 133 us (6.0 TB/s,
+// near the sweep's own bound); 1e7 points, m = 5, 69 -> 26 us and m = 8, 127 -> 35 us
+// (float64 issue); the finish 22 -> 5.5 us at m = 5 and 44 -> 8.2 us at m = 8.
 template <typename In, int U, int M>
 __global__ void __launch_bounds__(256)
     k_qr_sampled(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int64_t W, int mis,
@@ -905,10 +905,8 @@ __device__ inline bool last_block(const Work& w, int64_t blocks) {
 // data is known where it does not) is left to the rotations of that block alone.
 // Of a small fit only as many blocks take part as have a vector for every lane: the others'
 // parts would only be more to merge.
-constexpr int if_left_waves_per_eu(int M) { return M <= 3 ? 4 : 2; }
-
 template <typename In, int U, int M>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(if_left_waves_per_eu(M))))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(M <= 3 ? 4 : 2)))
     k_qr_if_left(FitDesc d, Work w, const In* __restrict__ x, const In* __restrict__ y, int mis, RangeArg ra,
                  double* __restrict__ coef, int32_t* __restrict__ status, double* __restrict__ info) {
     const int64_t left = w.tile_start[0];
@@ -951,9 +949,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(if_lef
 // levels of dependent rotations are what a whole fit of 64 points costs.  So up
 // to degree 4 short fits go 8 to a wave, as in the moment pass (3 levels, and 8
 // fits share them).  65,536 fits, float32, this pass: 16 points at degree 2
-// 184 -> 31 us; 64 points at degree 3 239 -> 66 us; 16 to 256 points at degree 3
-// 257 -> 114 us; 16 to 1,024 and more points unchanged within 2% (4,096 points 71
-// us before and after; 16 to 65,536 points 1.6 ms).  Above degree 4 the factor
+// 184 -> 24 us; 64 points at degree 3 239 -> 38 us; 16 to 256 points at degree 3
+// 257 -> 73 us; 4,096 fits of 4,096 points 73 us (71 before); 16 to 65,536 points
+// 1.6 ms both.  Above degree 4 the factor
 // alone takes most of the register file, so there the walk stays one fit at a
 // time, its descriptors read ahead.
 // 3 waves per SIMD up to degree 4 (4 before): at 4 both loops together left
