@@ -287,7 +287,7 @@ __device__ inline void block_merge_store(const Work& w, GivensQR<N>& q, int64_t 
 // dependence chain through each column's reciprocal.
 constexpr int qr_waves_per_eu(int M) { return M <= 2 ? 5 : (M <= 4 ? 4 : 2); }
 
-// the rows of waves W: wave `wave` of them, of block `block` of `blocks`
+// the share of wave `wave` of W, in block `block` of `blocks`
 template <typename In, int U, int M>
 __device__ __forceinline__ void qr_single_pass(const FitDesc& d, const Work& w, const In* __restrict__ x,
                                       const In* __restrict__ y, int64_t wave, int64_t W, int64_t block, int64_t blocks,
@@ -600,8 +600,8 @@ __device__ inline void gram_pass(const FitDesc& d, const Work& w, const In* __re
     single_block_partial<gram_len(M), gram_len(M)>(w, v);
 }
 
-// The pass, its prologue the sample basis in every
-// wave (about 0.7 us a degree, a chain of wave sums, behind the first loads).
+// The pass, its prologue the sample basis in every wave (about 0.7 us a degree, a
+// chain of wave sums, behind the first loads).
 // Measured against the rotations: 1e8 float32 points, m = 3, 346 -> 133 us (6.0 TB/s,
 // near the sweep's own bound); 1e7 points, m = 5, 69 -> 26 us and m = 8, 127 -> 35 us
 // (float64 issue); the finish 22 -> 5.5 us at m = 5 and 44 -> 8.2 us at m = 8.
@@ -629,12 +629,13 @@ enum SampledLeft { kNothingLeft = 0, kRotationsLeft = 1, kSecondPassLeft = 2 };
 // n / K |p_k|^2 for the sample's, the result is written when
 //  - every number is finite and every pivot positive;
 //  - H = E^(-1/2) P^T P E^(-1/2) has |H^(1/2)|_F^2 |H^(-1/2)|_F^2 <= 1.5 N^2 (N^2 for the
-//    identity; 32 N^2 at degree 2, any at degree 1): the pivots alone do not bound its condition.  Emulated on the CPU
-//    over x uniform, normal, Laplace, logistic, exponential, lognormal, Student, arcsine and
-//    in clusters, degrees 2 to 8, 1,025 to 60,001 points: the errors of fits accepted up to
-//    there are those of the rotations (a few 1e-16 at degree 4, 1e-15 to 1e-14 at 8),
-//    from degree 3 on they are larger past 4 N^2, tenfold past 30 N^2 (normal x, degree 8:
-//    5e-12 against 5e-14), at degree 2 past 100 N^2, at degree 1 nowhere;
+//    identity; 32 N^2 at degree 2, any at degree 1): the pivots alone do not bound its
+//    condition.  Emulated on the CPU over x uniform, normal, Laplace, logistic,
+//    exponential, lognormal, Student, arcsine and in clusters, degrees 1 to 8, 1,025 to
+//    60,001 points: the errors of fits accepted up to there are those of the rotations (a
+//    few 1e-16 at degree 4, 1e-15 to 1e-14 at 8); from degree 3 on they are larger past
+//    4 N^2, tenfold past 30 N^2 (normal x, degree 8: 5e-12 against 5e-14), at degree 2
+//    past 100 N^2, at degree 1 nowhere;
 //  - the correction, in this norm, is at most twice the solution: else its rounding, relative
 //    to the sample's noise, shows (values that are nearly all noise);
 //  - the be_k = ga_k ga_(k-1) of the monic recurrence (1/4 of the squared half-range
@@ -651,14 +652,15 @@ enum SampledLeft { kNothingLeft = 0, kRotationsLeft = 1, kSecondPassLeft = 2 };
 // and the solution in them, L^T de + D^-1 L^-1 P^T r; both go to the record for a second
 // pass, whose H is the identity to 2^40 roundings or so (emulated, up to 2^49: to 1e-3).
 template <int M>
-__device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Work& w, const double* sums, const double* rs,
-                                            bool first, double* __restrict__ coef, int32_t* __restrict__ status,
-                                            double* __restrict__ info) {
+__device__ __forceinline__ SampledLeft solve_sampled(const FitDesc& d, const Work& w, const double* sums,
+                                                     const double* rs, bool first, double* __restrict__ coef,
+                                                     int32_t* __restrict__ status, double* __restrict__ info) {
     constexpr int N = M + 1;
     OrthoBasis<M> B;
     B.load(rs);
     const double n = (double)d.n_single;
-    double A[N][N], z[N], step[M], e[N], lead[N];   // A: lower triangle, A[k][j] = G_jk; 1 / lead_k: leading coefficients
+    // A: lower triangle, A[k][j] = G_jk; 1 / lead_k: leading coefficients
+    double A[N][N], z[N], step[M], e[N], lead[N];
 #pragma unroll
     for (int k = 0; k < M; ++k) step[k] = recip(B.ga[k]);
     A[0][0] = n;
@@ -949,11 +951,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(M <= 3
 // levels of dependent rotations are what a whole fit of 64 points costs.  So up
 // to degree 4 short fits go 8 to a wave, as in the moment pass (3 levels, and 8
 // fits share them).  65,536 fits, float32, this pass: 16 points at degree 2
-// 184 -> 24 us; 64 points at degree 3 239 -> 38 us; 16 to 256 points at degree 3
-// 257 -> 73 us; 4,096 fits of 4,096 points 73 us (71 before); 16 to 65,536 points
-// 1.6 ms both.  Above degree 4 the factor
-// alone takes most of the register file, so there the walk stays one fit at a
-// time, its descriptors read ahead.
+// 184 -> 24 us; 64 points at degree 3 239 -> 38 us; 16 to 256 points (log-uniform) at
+// degrees 1 to 3 257 -> 117 us; 4,096 fits of 4,096 points 73 us (71 before); 16 to
+// 65,536 points 1.6 ms both.  Above degree 4 the factor alone takes most of the
+// register file, so there the walk stays one fit at a time, its descriptors read
+// ahead.
 // 3 waves per SIMD up to degree 4 (4 before): at 4 both loops together left
 // fits of 4,096 points 2 to 7% slower, at 3 they are no slower than before.
 // ---------------------------------------------------------------------------
